@@ -55,7 +55,7 @@ struct WsHeader {
   uint32_t nchunk[2];  // metric strip chunks pushed to the chunk kernels (count, fill pass)
   uint32_t nvwide;     // Voronoi cells listed for the 64-bit kernel (in vlist)
   uint32_t nvdone;     // workgroups of that kernel finished (the last one empties the list)
-  uint32_t nvstale;    // Voronoi rows listed for recomputation (in rank)
+  uint32_t nvstale;    // Voronoi rows listed for the general kernel (in rank)
   uint32_t nvfail;     // particles whose Voronoi row failed the last reuse test
   unsigned long long varea2;  // sum over Voronoi rows of a_t x a_{t+1} (six times the area covered)
   int32_t pad[48];
@@ -643,6 +643,12 @@ hipError_t launch_knn_fov_strips(const DevWs& w, int block, const float* theta, 
                                  int32_t* nbr, hipStream_t s);
 hipError_t launch_polar_order(const float* theta, int32_t n, double* sums, hipStream_t s);
 hipError_t launch_voronoi(const DevWs& w, int dmax, int32_t* ring, int32_t* deg, hipStream_t s);
+// Rows from staged strips of cells (of the particles marked in `stale`, or
+// all); the rows they leave are listed in rank / nvstale.  False, with
+// nothing launched, on grids that vor_strips_fit refuses.
+bool vor_strips_fit(const DevWs& w);
+bool launch_vor_strips(const DevWs& w, int dmax, int32_t* ring, int32_t* deg, const uint8_t* stale,
+                       const uint32_t* gate, hipStream_t s);
 hipError_t launch_voronoi_forces(const int32_t* x, const int32_t* y, int32_t n, int log2_box, int dmax,
                                  const int32_t* ring, const int32_t* deg, const nm_vm_params* p,
                                  double* area, double* perim, double* fx, double* fy, double* energy,

@@ -31,6 +31,10 @@
 // only, so it is not a neighbour.  The row then lists the remaining ones
 // counter-clockwise from the +x axis.
 //
+// These are the general kernels: they take the grids that are too coarse for
+// strips of cells, and the rows that the strip and wave kernels
+// (vorstrip.hip), which build most rows, leave.
+//
 // Two kernels.  The narrow one keeps offsets below 2^14 (16-bit pairs in
 // LDS, D in 64-bit integers) and a cell of at most 16 edges at any time;
 // cells it cannot finish within that range (sparse regions, long clipping
@@ -414,12 +418,12 @@ __device__ __forceinline__ void list_wide(const DevWs& w, bool go, int s) {
 }
 
 // Narrow kernel over slots: every slot (list == nullptr) or the slots listed
-// in `list` (count at *count).
-// With `gate`, nothing runs unless *gate != 0.
+// in `list` (count at *count), with `flagged` only those whose dflag is set
+// (and cleared here).  With `gate`, nothing runs unless *gate != 0.
 __global__ __launch_bounds__(kVnBlock) void k_voronoi(DevWs w, int dmax, int32_t* __restrict__ ring,
                                                       int32_t* __restrict__ deg,
                                                       const int32_t* __restrict__ list,
-                                                      const uint32_t* __restrict__ count,
+                                                      const uint32_t* __restrict__ count, int flagged,
                                                       const uint32_t* __restrict__ gate) {
   __shared__ int sxy[kVnCap * kVnBlock];
   __shared__ int sid[kVnCap * kVnBlock];
@@ -435,8 +439,13 @@ __global__ __launch_bounds__(kVnBlock) void k_voronoi(DevWs w, int dmax, int32_t
   const int k = base + threadIdx.x;
   bool wide = false;
   int s = -1;
-  if (k < nwork) {
-    s = list ? list[k] : k;
+  bool go = k < nwork;
+  if (go) s = list ? list[k] : k;
+  if (go && flagged) {
+    go = w.dflag[s] != 0;
+    if (go) w.dflag[s] = 0;
+  }
+  if (go) {
     const int4 e = w.sorted[s];
     Cell<kVnCap, kVnBlock, false> cell{sxy + threadIdx.x, nullptr, sid + threadIdx.x, 0, 0};
     const int rc = build_cell(w, cell, s, e.x, e.y, total);
@@ -454,6 +463,10 @@ __global__ __launch_bounds__(kVwBlock) void k_voronoi_wide(DevWs w, int dmax, in
   __shared__ int sid[kVwCap * kVwBlock];
   const int total = min(w.start[w.C], w.n);
   const int nl = static_cast<int>(min<uint32_t>(w.hdr->nvwide, static_cast<uint32_t>(w.n)));
+  if (nl == 0) {  // the usual case: no list to empty (512 same-address atomics: 10 us)
+    if (blockIdx.x == 0 && threadIdx.x == 0) w.hdr->nvstale = 0u;
+    return;
+  }
   for (int k = blockIdx.x * kVwBlock + threadIdx.x; k - threadIdx.x < nl; k += gridDim.x * kVwBlock) {
     if (k >= nl) continue;
     const int s = w.vlist[k];
@@ -467,6 +480,7 @@ __global__ __launch_bounds__(kVwBlock) void k_voronoi_wide(DevWs w, int dmax, in
     if (atomicAdd(&w.hdr->nvdone, 1u) == gridDim.x - 1) {
       w.hdr->nvwide = 0u;
       w.hdr->nvdone = 0u;
+      w.hdr->nvstale = 0u;  // (the narrow kernel's list is done with as well)
     }
   }
 }
@@ -726,19 +740,20 @@ __global__ __launch_bounds__(kBlock) void k_vor_check(const int32_t* __restrict_
 }
 
 // Rows that passed: rotate the site part to start at the +x axis again
-// (positions moved).  Stale rows: list the particle's slot for recomputation.
+// (positions moved).  Stale rows: with `list`, list the particle's slot for
+// recomputation.
 __global__ __launch_bounds__(kBlock) void k_vor_sweep(DevWs w, const int32_t* __restrict__ x,
                                                       const int32_t* __restrict__ y, int dmax,
                                                       int32_t* __restrict__ ring,
                                                       const int32_t* __restrict__ deg,
-                                                      const uint8_t* __restrict__ stale) {
+                                                      const uint8_t* __restrict__ stale, int list) {
   const int total = min(w.start[w.C], w.n);
   const int s = xcd_tile(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
   bool go = false;
   if (s < total) {
     const int i = w.sorted[s].z;
     if (stale[i]) {
-      go = true;
+      go = list != 0;
     } else {
       const int sh = 32 - w.log2_box;
       const int m = deg[i];
@@ -791,14 +806,28 @@ __global__ void k_vor_total(WsHeader* hdr, int log2_box, int32_t* out) {
 
 }  // namespace
 
-hipError_t launch_voronoi(const DevWs& w, int dmax, int32_t* ring, int32_t* deg, hipStream_t s) {
+namespace {
+
+// The general kernels over the listed slots (rank, nvstale; those whose dflag
+// is set with `flagged`), or over every slot when `every`; nothing runs when
+// `gate` is given and *gate is 0.
+hipError_t launch_general(const DevWs& w, int dmax, int32_t* ring, int32_t* deg, bool every, bool flagged,
+                          const uint32_t* gate, hipStream_t s) {
   const int nb = (w.n + kVnBlock - 1) / kVnBlock;
-  hipLaunchKernelGGL(k_voronoi, dim3(nb), dim3(kVnBlock), 0, s, w, dmax, ring, deg, nullptr, nullptr,
-                     nullptr);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_voronoi, dim3(nb), dim3(kVnBlock), 0, s, w, dmax, ring, deg, every ? nullptr : w.rank,
+                     every ? nullptr : &w.hdr->nvstale, flagged ? 1 : 0, gate);
   hipLaunchKernelGGL(k_voronoi_wide, dim3(kVwGrid), dim3(kVwBlock), 0, s, w, dmax, ring, deg);
   return hipGetLastError();
+}
+
+}  // namespace
+
+// Strips of cells first (vorstrip.hip), then the general kernels over the
+// rows that the strips leave; the general kernels alone on grids too coarse
+// for strips.
+hipError_t launch_voronoi(const DevWs& w, int dmax, int32_t* ring, int32_t* deg, hipStream_t s) {
+  const bool strips = launch_vor_strips(w, dmax, ring, deg, nullptr, nullptr, s);
+  return launch_general(w, dmax, ring, deg, !strips, strips, nullptr, s);
 }
 
 hipError_t launch_voronoi_check(const DevWs& w, const int32_t* x, const int32_t* y, int dmax,
@@ -816,25 +845,22 @@ hipError_t launch_voronoi_update(const DevWs& w, const int32_t* x, const int32_t
                                  int32_t* ring, int32_t* deg, uint8_t* stale, int32_t* nfail, int rounds,
                                  hipStream_t s) {
   const int nb = (w.n + kBlock - 1) / kBlock;
-  const int nv = (w.n + kVnBlock - 1) / kVnBlock;
+  const bool strips = vor_strips_fit(w);
+  const uint32_t* failed = &w.hdr->nvfail;
   hipError_t e = hipSuccess;
   for (int r = 0; r < rounds && e == hipSuccess; ++r) {
     e = launch_voronoi_check(w, x, y, dmax, ring, deg, stale, r == 0 ? nfail : nullptr, s);
     if (e != hipSuccess) break;
-    hipLaunchKernelGGL(k_vor_sweep, dim3(nb), dim3(kBlock), 0, s, w, x, y, dmax, ring, deg, stale);
-    hipLaunchKernelGGL(k_voronoi, dim3(nv), dim3(kVnBlock), 0, s, w, dmax, ring, deg, w.rank,
-                       &w.hdr->nvstale, nullptr);
-    hipLaunchKernelGGL(k_voronoi_wide, dim3(kVwGrid), dim3(kVwBlock), 0, s, w, dmax, ring, deg);
-    e = hipGetLastError();
+    hipLaunchKernelGGL(k_vor_sweep, dim3(nb), dim3(kBlock), 0, s, w, x, y, dmax, ring, deg, stale, strips ? 0 : 1);
+    if (strips) launch_vor_strips(w, dmax, ring, deg, stale, failed, s);
+    e = launch_general(w, dmax, ring, deg, false, strips, nullptr, s);
   }
   if (e != hipSuccess) return e;
   // final certificate; anything still stale: every row again
   e = launch_voronoi_check(w, x, y, dmax, ring, deg, stale, rounds == 0 ? nfail : nullptr, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_voronoi, dim3(nv), dim3(kVnBlock), 0, s, w, dmax, ring, deg, nullptr, nullptr,
-                     &w.hdr->nvfail);
-  hipLaunchKernelGGL(k_voronoi_wide, dim3(kVwGrid), dim3(kVwBlock), 0, s, w, dmax, ring, deg);
-  return hipGetLastError();
+  if (strips) launch_vor_strips(w, dmax, ring, deg, nullptr, failed, s);
+  return launch_general(w, dmax, ring, deg, !strips, strips, strips ? nullptr : failed, s);
 }
 
 }  // namespace nm

@@ -71,6 +71,56 @@ def test_voronoi_matches_oracle(kind, n, box, w):
     assert (ring[np.arange(ring.shape[1])[None, :] >= deg[:, None]] == -1).all()
 
 
+def _ring_of(m, box):
+    """One particle with m neighbours almost on a circle, in a sparser uniform background."""
+    x, y, _ = workloads.uniform(2000, box=box, seed_pos=77)
+    c, r = box // 2, box // 16
+    d2 = (x.astype(np.int64) - c) ** 2 + (y.astype(np.int64) - c) ** 2
+    x, y = x[d2 > (2 * r) ** 2], y[d2 > (2 * r) ** 2]
+    a = np.arange(m) * (2 * np.pi / m) + 0.01
+    return (np.concatenate([x, [c], c + np.rint(r * np.cos(a)).astype(np.int32)]).astype(np.int32),
+            np.concatenate([y, [c], c + np.rint(r * np.sin(a)).astype(np.int32)]).astype(np.int32))
+
+
+def _clump(n, dense, box, w):
+    """A uniform system with `dense` more particles inside two cells of width w, some of them coincident."""
+    x, y, _ = workloads.uniform(n, box=box, seed_pos=78)
+    cx, cy, _ = workloads.uniform(dense, box=w, seed_pos=79)
+    return (np.concatenate([x, 5 * w + 2 * cx]).astype(np.int32), np.concatenate([y, 7 * w + cy]).astype(np.int32))
+
+
+# Rows built from staged strips, by a wavefront each, or by the general
+# kernels: grids on both sides of what strips take (blocks of 3 to 15 cells,
+# 16-bit and 32-bit offsets, a halo as wide as the box), strips whose halo
+# overflows, rows of more than 16 entries, coincident particles in both.
+STRIP_CASES = [("uniform", 513, 1 << 12, 1 << 9), ("uniform", 513, 1 << 12, 1 << 8), ("uniform", 513, 1 << 20, 1 << 15),
+               ("uniform", 4099, 1 << 15, 1 << 7), ("uniform", 4099, 1 << 18, 1 << 12), ("uniform", 4099, 1 << 17, 1 << 12),
+               ("uniform", 4099, 1 << 20, 1 << 13), ("uniform", 9001, 1 << 14, 1 << 10), ("uniform", 65, 1 << 10, 1 << 7),
+               ("ring15", 0, 1 << 14, 1 << 9), ("ring17", 0, 1 << 14, 1 << 9), ("ring60", 0, 1 << 14, 1 << 8),
+               ("ring60", 0, 1 << 20, 1 << 15), ("clump", 4000, 1 << 14, 1 << 8), ("clump", 4000, 1 << 20, 1 << 14)]
+
+
+@pytest.mark.parametrize("kind,n,box,w", STRIP_CASES)
+def test_voronoi_strip_wave_and_general_rows_match_oracle(kind, n, box, w):
+    if kind.startswith("ring"):
+        x, y = _ring_of(int(kind[4:]), box)
+    elif kind == "clump":
+        x, y = _clump(n, 3000, box, w)
+    else:
+        x, y, _ = workloads.uniform(n, box=box, seed_pos=n + w)
+    try:
+        ref = _oracle_rows(x, y, box)
+    except oracle.OracleError as e:
+        assert e.status == oracle.E_RANGE
+        assert _gpu_rows(x, y, box, w, dmax=64)[2] == nm.NM_E_RANGE
+        return
+    for dmax in (64, max(len(r) for r in ref)):
+        ring, deg, st, _ = _gpu_rows(x, y, box, w, dmax=dmax)
+        assert st == 0
+        assert _rows_of(ring, deg) == ref
+        assert (ring[np.arange(dmax)[None, :] >= deg[:, None]] == -1).all()
+
+
 @pytest.mark.parametrize("m,box,wdiv", [(32, 1 << 20, 1), (32, 1 << 20, 2), (64, 1 << 16, 1), (64, 1 << 16, 4)])
 def test_voronoi_square_lattice_degenerate(m, box, wdiv):
     # four co-circular particles at every lattice square: only the axis neighbours
