@@ -52,7 +52,6 @@ __device__ __forceinline__ void ws_init_body(const DevWs& w, int b, int nb) {
       w.hdr->nvdone = 0u;
       w.hdr->nvstale = 0u;
       w.hdr->nvfail = 0u;
-      w.hdr->varea2 = 0ull;
     }
   }
 }

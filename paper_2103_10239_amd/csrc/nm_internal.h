@@ -12,7 +12,8 @@
 //                            of the noise, fused step only
 //   dflag       uint8[n]     1 for a slot whose k-NN search is deferred (kept 0
 //                            between launches)
-//   chunks      int4[cap]    row chunks of dense metric strips, cap = n / 32 + 1024
+//   chunks      int4[cap]    row chunks of dense metric strips, cap = n / 32 + 1024;
+//                            the Voronoi reuse test's per-workgroup failures and areas
 //   vlist       int32[n]     slots of Voronoi cells handed to the 64-bit kernel
 //   coarse      int4[n]      particles in coarse-bin order (two-level binning)
 //   hist        int32[nbins * nblk + 1]  per-workgroup coarse-bin counts, then
@@ -57,8 +58,8 @@ struct WsHeader {
   uint32_t nvdone;     // workgroups of that kernel finished (the last one empties the list)
   uint32_t nvstale;    // Voronoi rows listed for the general kernel (in rank)
   uint32_t nvfail;     // particles whose Voronoi row failed the last reuse test
-  unsigned long long varea2;  // sum over Voronoi rows of a_t x a_{t+1} (six times the area covered)
-  int32_t pad[48];
+  uint32_t nvgo;       // rows failed in the update's last reuse test
+  int32_t pad[49];
 };
 static_assert(sizeof(WsHeader) == 256, "header is one 256-byte block");
 

@@ -513,14 +513,12 @@ __global__ __launch_bounds__(kVwBlock) void k_voronoi_wide(DevWs w, int dmax, in
 // rows of co-circular particles (a square lattice) never pass, so such
 // systems are always recomputed.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kBlock) void k_vor_clear(WsHeader* hdr, uint8_t* __restrict__ stale, int n) {
+// `again`: a later round of the update, which runs only while rows failed.
+__global__ __launch_bounds__(kBlock) void k_vor_clear(WsHeader* hdr, uint8_t* __restrict__ stale, int n, int again) {
+  if (again && hdr->nvgo == 0u) return;
   const int i = blockIdx.x * kBlock + threadIdx.x;
   if (i < n) stale[i] = 0;
-  if (i == 0) {
-    hdr->nvfail = 0u;
-    hdr->nvstale = 0u;
-    hdr->varea2 = 0ull;
-  }
+  if (i == 0) hdr->nvstale = 0u;
 }
 
 // Rows of up to this many entries are read whole when searched.
@@ -608,121 +606,330 @@ __device__ __forceinline__ bool row_holds_then(const RowView& rv, int bxp, int b
   return false;
 }
 
-__global__ __launch_bounds__(kBlock) void k_vor_check(const int32_t* __restrict__ x,
-                                                      const int32_t* __restrict__ y, int n, int log2_box,
+// The reuse test of row i in general: rows of any length, coincident particles.
+struct RowCheck {
+  bool fail;
+  int turn, own;  // the site part starts after `own` entries and has to turn left by `turn`
+  long long area2;
+};
+
+__device__ __noinline__ RowCheck vor_check_row(const int32_t* __restrict__ x, const int32_t* __restrict__ y, int n,
+                                               int log2_box, int dmax, const int32_t* __restrict__ ring,
+                                               const int32_t* __restrict__ deg, int i) {
+  const int sh = 32 - log2_box;
+  const int quarter = 1 << (log2_box - 2);
+  const int m = deg[i];
+  const int32_t* row = ring + static_cast<long long>(i) * dmax;
+  bool fail = false;
+  int turn = 0, own = 0;
+  long long area2 = 0;
+  if (m < 3 || m > dmax) fail = true;
+  for (int t = 0; t < m && !fail; ++t) {  // indices first: only valid ones are read through
+    const int j = row[t];
+    if (static_cast<unsigned>(j) >= static_cast<unsigned>(n) || j == i) fail = true;
+  }
+  if (!fail) {
+    const int xi = x[i], yi = y[i];
+    const RowView rv = row_view(row, m, i, x, y, dmax);
+    own = rv.own;
+    // the own site counts once in the area total: from its lowest index;
+    // and every particle listed at the own site lists this one back
+    bool lowest = true;
+    for (int t = 0; t < rv.own && !fail; ++t) {
+      const int p = row[t];
+      lowest = lowest && p > i;
+      const int mp = deg[p];
+      bool back = false;
+      if (mp >= 1 && mp <= dmax) {
+        const int32_t* rowp = ring + static_cast<long long>(p) * dmax;
+        for (int u = 0; u < mp; ++u) {
+          const int q = rowp[u];
+          if (static_cast<unsigned>(q) >= static_cast<unsigned>(n) || x[q] != xi || y[q] != yi) break;
+          back = back || q == i;
+        }
+      }
+      if (!back) fail = true;
+    }
+    if (m - rv.own < 3) fail = true;
+    auto off = [&](int t, int& ox, int& oy) {  // entry t's offset
+      ox = wrap_axis(rv.xat(t) - xi, sh);
+      oy = wrap_axis(rv.yat(t) - yi, sh);
+    };
+    const int t0 = fail ? 0 : rv.site_start(rv.own);
+    int ta = t0, tb = fail ? 0 : rv.next_site(t0);
+    int ax, ay, bx, by;
+    if (!fail) {
+      off(ta, ax, ay);
+      off(tb, bx, by);
+    }
+    int wraps = 0, nsites = 0;
+    for (int guard = 0; guard < m && !fail; ++guard) {
+      const int tc = rv.next_site(tb);
+      int cx, cy;
+      off(tc, cx, cy);
+      if (abs(ax) >= quarter || abs(ay) >= quarter || (ax == 0 && ay == 0)) {
+        fail = true;
+        break;
+      }
+      const long long cr = static_cast<long long>(ax) * by - static_cast<long long>(ay) * bx;
+      if (cr <= 0) fail = true;
+      area2 += cr;
+      if (!ccw_before(ax, ay, bx, by)) {
+        ++wraps;
+        turn = tb - rv.own;
+      }
+      if (inc_sign_w(ax, ay, bx, by, cx, cy) <= 0) fail = true;
+      const int a = rv.idx(ta);
+      const int ma = deg[a];
+      if (ma < 3 || ma > dmax) {
+        fail = true;
+      } else {
+        // a's row must hold b's site directly followed by i's site.  When it
+        // lists b directly followed by i the sites are adjacent (b and i lie
+        // at different positions) and no position is needed; otherwise the
+        // row is walked site by site.
+        const int32_t* rowa = ring + static_cast<long long>(a) * dmax;
+        const int b = rv.idx(tb);
+        bool okidx = true, adjacent = false;
+        if (ma <= kRowRead && dmax >= kRowRead) {
+          // the usual short row: its first kRowRead entries read together
+          // (rows are dmax long), instead of one read per step
+          int ra[kRowRead];
+#pragma unroll
+          for (int u = 0; u < kRowRead; ++u) ra[u] = rowa[u];
+#pragma unroll
+          for (int u = 0; u < kRowRead; ++u) {
+            if (u < ma) {
+              const int nx = u + 1 < ma ? ra[u + 1 < kRowRead ? u + 1 : 0] : ra[0];
+              okidx = okidx && static_cast<unsigned>(ra[u]) < static_cast<unsigned>(n);
+              adjacent = adjacent || (ra[u] == b && nx == i);
+            }
+          }
+        } else {
+          for (int u = 0; u < ma; ++u) {
+            const int q = rowa[u];
+            okidx = okidx && static_cast<unsigned>(q) < static_cast<unsigned>(n);
+            adjacent = adjacent || (q == b && rowa[u + 1 < ma ? u + 1 : 0] == i);
+          }
+        }
+        if (!okidx || (!adjacent && !row_holds_then(row_view(rowa, ma, a, x, y, dmax), rv.xat(tb), rv.yat(tb), xi, yi)))
+          fail = true;
+      }
+      ++nsites;
+      ta = tb;
+      ax = bx;
+      ay = by;
+      tb = tc;
+      bx = cx;
+      by = cy;
+      if (ta == t0) break;
+    }
+    if (wraps != 1 || nsites < 3) fail = true;
+    if (!lowest) area2 = 0;
+  }
+  return {fail, turn, own, area2};
+}
+
+// Sign of the incircle determinant na (b x c) + nb (c x a) + nc (a x b) from
+// its exact fp64 norms and cross products (below 2^41): the products round
+// within 2^-53 of themselves, so the sign is that of the sum wherever the sum
+// exceeds 2^-50 of their magnitudes; elsewhere 128-bit integers decide.
+__device__ __forceinline__ bool inc_positive(double na, double nb, double nc, double bc, double ca, double ab) {
+  const double p = na * bc, q = nb * ca, r = nc * ab;
+  const double d = p + q + r;
+  const double e = (fabs(p) + fabs(q) + fabs(r)) * 0x1p-50;
+  if (d > e) return true;
+  if (d < -e) return false;
+  const auto big = [](double v) { return static_cast<__int128>(static_cast<long long>(v)); };
+  return big(na) * big(bc) + big(nb) * big(ca) + big(nc) * big(ab) > 0;
+}
+
+// Rows of up to this many entries without coincident particles take the
+// straight path (longer ones are one row in ten thousand of a uniform system).
+constexpr int kRowFast = 12;
+
+// The usual row: its entries and their positions read together and held in
+// registers under fixed indices (a walk by index costs a select over the row
+// per access), the norms and cross products shared between neighbouring
+// triangles, incircle signs from fp64.  Returns false where the general test
+// has to decide (long rows, coincident particles, a row that does not list
+// the triangle entry by entry).
+__device__ __forceinline__ bool vor_check_fast(const int32_t* __restrict__ x, const int32_t* __restrict__ y, int n,
+                                               int log2_box, int dmax, const int32_t* __restrict__ ring,
+                                               const int32_t* __restrict__ deg, int i, RowCheck& out) {
+  const int m = deg[i];
+  if (m < 3 || m > kRowFast || dmax < kRowFast) return false;
+  const int sh = 32 - log2_box;
+  const int quarter = 1 << (log2_box - 2);
+  const int32_t* row = ring + static_cast<long long>(i) * dmax;
+  int rw[kRowFast], ox[kRowFast], oy[kRowFast];
+#pragma unroll
+  for (int u = 0; u < kRowFast; u += 4) {
+    const nm_int4u v = *reinterpret_cast<const nm_int4u*>(row + u);
+    rw[u] = v[0];
+    rw[u + 1] = v[1];
+    rw[u + 2] = v[2];
+    rw[u + 3] = v[3];
+  }
+  bool bad = false;
+#pragma unroll
+  for (int u = 0; u < kRowFast; ++u)
+    if (u < m) bad = bad || static_cast<unsigned>(rw[u]) >= static_cast<unsigned>(n) || rw[u] == i;
+  if (bad) {
+    out = {true, 0, 0, 0};
+    return true;
+  }
+  const int xi = x[i], yi = y[i];
+#pragma unroll
+  for (int u = 0; u < kRowFast; ++u) {
+    ox[u] = u < m ? x[rw[u]] : xi;
+    oy[u] = u < m ? y[rw[u]] : yi;
+  }
+#pragma unroll
+  for (int u = 0; u < kRowFast; ++u) {
+    ox[u] = wrap_axis(ox[u] - xi, sh);
+    oy[u] = wrap_axis(oy[u] - yi, sh);
+  }
+  bool fail = false, twin = false;
+  int wraps = 0, turn = 0;
+  double area2 = 0.0;  // integers below 2^45
+  double ax = ox[0], ay = oy[0], bx = ox[1], by = oy[1];
+  double na = ax * ax + ay * ay, nb = bx * bx + by * by, ab = ax * by - ay * bx;
+#pragma unroll
+  for (int u = 0; u < kRowFast; ++u) {
+    if (u < m) {
+      // entries u, u + 1 and u + 2 of the cycle; the next one (u + 2) here
+      const int w1 = u + 2 < kRowFast ? u + 2 : 0;
+      const int cxi = u + 2 < m ? ox[w1] : (u + 2 == m ? ox[0] : ox[1]);
+      const int cyi = u + 2 < m ? oy[w1] : (u + 2 == m ? oy[0] : oy[1]);
+      const double cx = cxi, cy = cyi;
+      const double nc = cx * cx + cy * cy, bc = bx * cy - by * cx, ca = cx * ay - cy * ax;
+      if (abs(ox[u]) >= quarter || abs(oy[u]) >= quarter) fail = true;
+      twin = twin || na == 0.0 || (ax == bx && ay == by);
+      if (!(ab > 0.0)) fail = true;
+      area2 += ab;
+      if (!ccw_before(static_cast<int>(ax), static_cast<int>(ay), static_cast<int>(bx), static_cast<int>(by))) {
+        ++wraps;
+        turn = u + 1 < m ? u + 1 : 0;
+      }
+      if (!inc_positive(na, nb, nc, bc, ca, ab)) fail = true;
+      ax = bx;
+      ay = by;
+      bx = cx;
+      by = cy;
+      na = nb;
+      nb = nc;
+      ab = bc;
+    }
+  }
+  if (twin) return false;
+  if (wraps != 1) fail = true;
+  // entry u's row must list entry u + 1 directly followed by i; the rows (and
+  // lengths) of kRowBatch entries are read together
+  bool unlisted = false;
+  constexpr int kRowBatch = 4;
+#pragma unroll
+  for (int u0 = 0; u0 < kRowFast; u0 += kRowBatch) {
+    if (u0 < m && !fail && !unlisted) {
+      int ma[kRowBatch], ra[kRowBatch][8];
+#pragma unroll
+      for (int c = 0; c < kRowBatch; ++c) {
+        const int a = u0 + c < m ? rw[u0 + c] : i;
+        const int32_t* rowa = ring + static_cast<long long>(a) * dmax;
+        ma[c] = deg[a];
+#pragma unroll
+        for (int v = 0; v < 8; v += 4) {
+          const nm_int4u q = *reinterpret_cast<const nm_int4u*>(rowa + v);
+          ra[c][v] = q[0];
+          ra[c][v + 1] = q[1];
+          ra[c][v + 2] = q[2];
+          ra[c][v + 3] = q[3];
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < kRowBatch; ++c) {
+        const int u = u0 + c;
+        if (u >= m) continue;
+        const int a = rw[u], b = u + 1 < m ? rw[u + 1 < kRowFast ? u + 1 : 0] : rw[0];
+        const int mc = ma[c];
+        if (mc < 3 || mc > kRowFast) {
+          unlisted = true;
+          continue;
+        }
+        int tail[4] = {-1, -1, -1, -1};
+        if (mc > 8) {
+          const nm_int4u q = *reinterpret_cast<const nm_int4u*>(ring + static_cast<long long>(a) * dmax + 8);
+          tail[0] = q[0];
+          tail[1] = q[1];
+          tail[2] = q[2];
+          tail[3] = q[3];
+        }
+        auto at = [&](int v) { return v < 8 ? ra[c][v & 7] : tail[v & 3]; };
+        bool in = true, next = false;
+#pragma unroll
+        for (int v = 0; v < kRowFast; ++v) {
+          if (v < mc) {
+            const int nx = v + 1 < mc ? at(v + 1 < kRowFast ? v + 1 : 0) : at(0);
+            in = in && static_cast<unsigned>(at(v)) < static_cast<unsigned>(n);
+            next = next || (at(v) == b && nx == i);
+          }
+        }
+        if (!in) fail = true;
+        if (!next) unlisted = true;
+      }
+    }
+  }
+  if (!fail && unlisted) return false;
+  out = {fail, fail ? 0 : turn, 0, static_cast<long long>(area2)};
+  return true;
+}
+
+// kOrdered: the particles in the order of the cells in w (built for x, y), so
+// that the rows and positions which neighbouring lanes read are the same few
+// lines (in the caller's order every one is a line of its own from memory);
+// rot[slot] then gets how far the row's site part has to turn left to start at
+// the +x axis (0 for rows that failed).  A particle left out of the cells
+// (outside the box) is flagged by the binning and keeps its row.
+//
+// Bound by the gathers (about 40 lines a lane: the row, its entries'
+// positions, their rows).  The check of 2^20 moved particles: 0.52 ms with
+// every row walked by index in the caller's order, 0.48 in cell order, 0.41
+// without the atomics, 0.22 with short rows held in registers, the norms and
+// cross products shared and the signs from fp64; four waves per SIMD (the
+// compiler would take 177 registers and two).
+template <bool kOrdered>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_vor_check(const int32_t* __restrict__ x,
+                                                      const int32_t* __restrict__ y, DevWs w,
                                                       int dmax, const int32_t* __restrict__ ring,
                                                       const int32_t* __restrict__ deg,
-                                                      uint8_t* __restrict__ stale, WsHeader* hdr) {
-  const int i = blockIdx.x * kBlock + threadIdx.x;
+                                                      uint8_t* __restrict__ stale, int32_t* __restrict__ rot,
+                                                      int again) {
+  WsHeader* hdr = w.hdr;
+  if (again && hdr->nvgo == 0u) return;
+  if (kOrdered && !cells_built(w)) {
+    if (threadIdx.x == 0) {
+      if (blockIdx.x == 0) set_err(hdr, NM_E_INVAL);
+      w.chunks[blockIdx.x] = make_int4(0, 0, 0, 0);
+    }
+    return;
+  }
+  const int n = w.n, log2_box = w.log2_box;
+  int i = kOrdered ? xcd_tile(blockIdx.x, gridDim.x) * kBlock + threadIdx.x : blockIdx.x * kBlock + threadIdx.x;
+  const int slot = i;
+  if (kOrdered) i = slot < min(w.start[w.C], n) ? w.sorted[slot].z : n;
   bool fail = false;
   long long area2 = 0;
   if (i < n) {
-    const int sh = 32 - log2_box;
-    const int quarter = 1 << (log2_box - 2);
-    const int m = deg[i];
-    const int32_t* row = ring + static_cast<long long>(i) * dmax;
-    if (m < 3 || m > dmax) fail = true;
-    for (int t = 0; t < m && !fail; ++t) {  // indices first: only valid ones are read through
-      const int j = row[t];
-      if (static_cast<unsigned>(j) >= static_cast<unsigned>(n) || j == i) fail = true;
-    }
-    if (!fail) {
-      const int xi = x[i], yi = y[i];
-      const RowView rv = row_view(row, m, i, x, y, dmax);
-      // the own site counts once in the area total: from its lowest index;
-      // and every particle listed at the own site lists this one back
-      bool lowest = true;
-      for (int t = 0; t < rv.own && !fail; ++t) {
-        const int p = row[t];
-        lowest = lowest && p > i;
-        const int mp = deg[p];
-        bool back = false;
-        if (mp >= 1 && mp <= dmax) {
-          const int32_t* rowp = ring + static_cast<long long>(p) * dmax;
-          for (int u = 0; u < mp; ++u) {
-            const int q = rowp[u];
-            if (static_cast<unsigned>(q) >= static_cast<unsigned>(n) || x[q] != xi || y[q] != yi) break;
-            back = back || q == i;
-          }
-        }
-        if (!back) fail = true;
-      }
-      if (m - rv.own < 3) fail = true;
-      auto off = [&](int t, int& ox, int& oy) {  // entry t's offset
-        ox = wrap_axis(rv.xat(t) - xi, sh);
-        oy = wrap_axis(rv.yat(t) - yi, sh);
-      };
-      const int t0 = fail ? 0 : rv.site_start(rv.own);
-      int ta = t0, tb = fail ? 0 : rv.next_site(t0);
-      int ax, ay, bx, by;
-      if (!fail) {
-        off(ta, ax, ay);
-        off(tb, bx, by);
-      }
-      int wraps = 0, nsites = 0;
-      for (int guard = 0; guard < m && !fail; ++guard) {
-        const int tc = rv.next_site(tb);
-        int cx, cy;
-        off(tc, cx, cy);
-        if (abs(ax) >= quarter || abs(ay) >= quarter || (ax == 0 && ay == 0)) {
-          fail = true;
-          break;
-        }
-        const long long cr = static_cast<long long>(ax) * by - static_cast<long long>(ay) * bx;
-        if (cr <= 0) fail = true;
-        area2 += cr;
-        if (!ccw_before(ax, ay, bx, by)) ++wraps;
-        if (inc_sign_w(ax, ay, bx, by, cx, cy) <= 0) fail = true;
-        const int a = rv.idx(ta);
-        const int ma = deg[a];
-        if (ma < 3 || ma > dmax) {
-          fail = true;
-        } else {
-          // a's row must hold b's site directly followed by i's site.  When it
-          // lists b directly followed by i the sites are adjacent (b and i lie
-          // at different positions) and no position is needed; otherwise the
-          // row is walked site by site.
-          const int32_t* rowa = ring + static_cast<long long>(a) * dmax;
-          const int b = rv.idx(tb);
-          bool okidx = true, adjacent = false;
-          if (ma <= kRowRead && dmax >= kRowRead) {
-            // the usual short row: its first kRowRead entries read together
-            // (rows are dmax long), instead of one read per step
-            int ra[kRowRead];
-#pragma unroll
-            for (int u = 0; u < kRowRead; ++u) ra[u] = rowa[u];
-#pragma unroll
-            for (int u = 0; u < kRowRead; ++u) {
-              if (u < ma) {
-                const int nx = u + 1 < ma ? ra[u + 1 < kRowRead ? u + 1 : 0] : ra[0];
-                okidx = okidx && static_cast<unsigned>(ra[u]) < static_cast<unsigned>(n);
-                adjacent = adjacent || (ra[u] == b && nx == i);
-              }
-            }
-          } else {
-            for (int u = 0; u < ma; ++u) {
-              const int q = rowa[u];
-              okidx = okidx && static_cast<unsigned>(q) < static_cast<unsigned>(n);
-              adjacent = adjacent || (q == b && rowa[u + 1 < ma ? u + 1 : 0] == i);
-            }
-          }
-          if (!okidx || (!adjacent && !row_holds_then(row_view(rowa, ma, a, x, y, dmax), rv.xat(tb), rv.yat(tb), xi, yi)))
-            fail = true;
-        }
-        ++nsites;
-        ta = tb;
-        ax = bx;
-        ay = by;
-        tb = tc;
-        bx = cx;
-        by = cy;
-        if (ta == t0) break;
-      }
-      if (wraps != 1 || nsites < 3) fail = true;
-      if (!lowest) area2 = 0;
-    }
+    RowCheck r{};
+    if (!vor_check_fast(x, y, n, log2_box, dmax, ring, deg, i, r))
+      r = vor_check_row(x, y, n, log2_box, dmax, ring, deg, i);
+    fail = r.fail;
+    area2 = r.area2;
+    if (kOrdered) rot[slot] = fail || r.turn == 0 ? 0 : r.turn | r.own << 16;
     if (fail) {
       stale[i] = 1;
+      const int m = deg[i];
+      const int32_t* row = ring + static_cast<long long>(i) * dmax;
       const int m2 = min(max(m, 0), dmax);  // deg out of range: mark what the row holds
       for (int t = 0; t < m2; ++t) {
         const int j = row[t];
@@ -730,62 +937,70 @@ __global__ __launch_bounds__(kBlock) void k_vor_check(const int32_t* __restrict_
       }
     }
   }
-  const unsigned long long bal = __ballot(fail);
-  if (bal != 0ull && (threadIdx.x & 63) == __ffsll(static_cast<long long>(bal)) - 1)
-    atomicAdd(&hdr->nvfail, static_cast<uint32_t>(__popcll(bal)));
-  // the area total: a wavefront's sum, one atomic (only counted while no row fails)
+  // The workgroup's failures and area (that counts only while no row fails)
+  // go to its entry of the metric lists' chunk table, which is free between
+  // their calls; k_vor_total adds them up (an atomic per wavefront and counter
+  // on one address each: 580 us for the first round at 2^20, 440 without).
+  __shared__ long long s_area[kBlock / 64];
+  __shared__ int s_fail[kBlock / 64];
+  const int nf = __popcll(__ballot(fail));
   if (fail) area2 = 0;
   for (int o = 32; o > 0; o >>= 1) area2 += __shfl_xor(area2, o, 64);
-  if ((threadIdx.x & 63) == 0 && area2 != 0) atomicAdd(&hdr->varea2, static_cast<unsigned long long>(area2));
+  if ((threadIdx.x & 63) == 0) {
+    s_area[threadIdx.x >> 6] = area2;
+    s_fail[threadIdx.x >> 6] = nf;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    long long a = 0;
+    int f = 0;
+#pragma unroll
+    for (int q = 0; q < kBlock / 64; ++q) {
+      a += s_area[q];
+      f += s_fail[q];
+    }
+    w.chunks[blockIdx.x] = make_int4(static_cast<int>(a), static_cast<int>(a >> 32), f, 0);
+  }
 }
 
 // Rows that passed: rotate the site part to start at the +x axis again
-// (positions moved).  Stale rows: with `list`, list the particle's slot for
-// recomputation.
-__global__ __launch_bounds__(kBlock) void k_vor_sweep(DevWs w, const int32_t* __restrict__ x,
-                                                      const int32_t* __restrict__ y, int dmax,
-                                                      int32_t* __restrict__ ring,
+// (positions moved) by the turn that the check found.  Without strips, the
+// slots of stale rows are then listed for recomputation (k_vor_list).
+__global__ __launch_bounds__(kBlock) void k_vor_sweep(DevWs w, int dmax, int32_t* __restrict__ ring,
                                                       const int32_t* __restrict__ deg,
-                                                      const uint8_t* __restrict__ stale, int list) {
+                                                      const uint8_t* __restrict__ stale,
+                                                      const int32_t* __restrict__ rot, int again) {
+  if ((again && w.hdr->nvgo == 0u) || !cells_built(w)) return;
   const int total = min(w.start[w.C], w.n);
   const int s = xcd_tile(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
-  bool go = false;
-  if (s < total) {
-    const int i = w.sorted[s].z;
-    if (stale[i]) {
-      go = list != 0;
-    } else {
-      const int sh = 32 - w.log2_box;
-      const int m = deg[i];
-      int32_t* row = ring + static_cast<long long>(i) * dmax;
-      const RowView rv = row_view(row, m, i, x, y, dmax);
-      const int xi = x[i], yi = y[i];
-      // the first entry of the site with the smallest angle
-      int t0 = rv.own;
-      int bx = wrap_axis(rv.xat(t0) - xi, sh), by = wrap_axis(rv.yat(t0) - yi, sh);
-      for (int t = rv.own + 1; t < m; ++t) {
-        const int ox = wrap_axis(rv.xat(t) - xi, sh), oy = wrap_axis(rv.yat(t) - yi, sh);
-        if (ccw_before(ox, oy, bx, by)) {
-          t0 = t;
-          bx = ox;
-          by = oy;
-        }
-      }
-      t0 = rv.site_start(t0);
-      if (t0 != rv.own) {  // rotate the site part left by t0 - own: three reversals
-        auto rev = [&](int lo, int hi) {
-          for (--hi; lo < hi; ++lo, --hi) {
-            const int v = row[lo];
-            row[lo] = row[hi];
-            row[hi] = v;
-          }
-        };
-        rev(rv.own, t0);
-        rev(t0, m);
-        rev(rv.own, m);
-      }
+  if (s >= total) return;
+  const int t = rot[s];
+  if (t == 0) return;
+  const int i = w.sorted[s].z;
+  if (stale[i]) return;
+  // the site part left by t: three reversals (the own site's particles, which
+  // come first, lie between the row's start and the part)
+  const int m = deg[i];
+  int32_t* row = ring + static_cast<long long>(i) * dmax;
+  const int own = t >> 16, left = t & 0xFFFF;
+  auto rev = [&](int lo, int hi) {
+    for (--hi; lo < hi; ++lo, --hi) {
+      const int v = row[lo];
+      row[lo] = row[hi];
+      row[hi] = v;
     }
-  }
+  };
+  rev(own, own + left);
+  rev(own + left, m);
+  rev(own, m);
+}
+
+// The slots of stale rows, for the general kernel on grids without strips.
+__global__ __launch_bounds__(kBlock) void k_vor_list(DevWs w, const uint8_t* __restrict__ stale, int again) {
+  if ((again && w.hdr->nvgo == 0u) || !cells_built(w)) return;
+  const int total = min(w.start[w.C], w.n);
+  const int s = xcd_tile(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
+  const bool go = s < total && stale[w.sorted[s].z] != 0;
   const unsigned long long b = __ballot(go);
   if (b == 0ull) return;
   const int lane = threadIdx.x & 63;
@@ -797,11 +1012,40 @@ __global__ __launch_bounds__(kBlock) void k_vor_sweep(DevWs w, const int32_t* __
   if (go && at < static_cast<uint32_t>(w.n)) w.rank[at] = s;
 }
 
-// After k_vor_check: a total other than 6 L^2 distrusts every row.
-__global__ void k_vor_total(WsHeader* hdr, int log2_box, int32_t* out) {
-  const unsigned long long want = 6ull << (2 * log2_box);
-  if (hdr->nvfail == 0u && hdr->varea2 != want) hdr->nvfail = 0x80000000u;
-  if (out) *out = static_cast<int32_t>(min(hdr->nvfail, 0x7FFFFFFFu));
+// After k_vor_check (nb workgroups): how many rows failed; a total area other
+// than 6 L^2 distrusts every row.  The update's later rounds run while rows
+// fail (nvgo).  One workgroup; the counts and areas are integers, so their
+// order does not matter.
+__global__ __launch_bounds__(kBlock) void k_vor_total(DevWs w, int nb, int32_t* out, int again) {
+  WsHeader* hdr = w.hdr;
+  if (again && hdr->nvgo == 0u) return;
+  __shared__ unsigned long long s_area[kBlock];
+  __shared__ uint32_t s_fail[kBlock];
+  unsigned long long area = 0;
+  uint32_t fails = 0;
+  for (int b = threadIdx.x; b < nb; b += kBlock) {
+    const int4 v = w.chunks[b];
+    area += static_cast<unsigned long long>(static_cast<uint32_t>(v.x)) |
+            static_cast<unsigned long long>(static_cast<uint32_t>(v.y)) << 32;
+    fails += static_cast<uint32_t>(v.z);
+  }
+  s_area[threadIdx.x] = area;
+  s_fail[threadIdx.x] = fails;
+  __syncthreads();
+  for (int h = kBlock / 2; h > 0; h >>= 1) {
+    if (static_cast<int>(threadIdx.x) < h) {
+      s_area[threadIdx.x] += s_area[threadIdx.x + h];
+      s_fail[threadIdx.x] += s_fail[threadIdx.x + h];
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x != 0) return;
+  const unsigned long long want = 6ull << (2 * w.log2_box);
+  uint32_t nf = s_fail[0];
+  if (nf == 0u && s_area[0] != want) nf = 0x80000000u;
+  hdr->nvfail = nf;
+  hdr->nvgo = nf != 0u ? 1u : 0u;
+  if (out) *out = static_cast<int32_t>(min(nf, 0x7FFFFFFFu));
 }
 
 }  // namespace
@@ -834,33 +1078,36 @@ hipError_t launch_voronoi_check(const DevWs& w, const int32_t* x, const int32_t*
                                 const int32_t* ring, const int32_t* deg, uint8_t* stale, int32_t* nfail,
                                 hipStream_t s) {
   const int nb = (w.n + kBlock - 1) / kBlock;
-  hipLaunchKernelGGL(k_vor_clear, dim3(nb), dim3(kBlock), 0, s, w.hdr, stale, w.n);
-  hipLaunchKernelGGL(k_vor_check, dim3(nb), dim3(kBlock), 0, s, x, y, w.n, w.log2_box, dmax, ring, deg,
-                     stale, w.hdr);
-  hipLaunchKernelGGL(k_vor_total, dim3(1), dim3(1), 0, s, w.hdr, w.log2_box, nfail);
+  hipLaunchKernelGGL(k_vor_clear, dim3(nb), dim3(kBlock), 0, s, w.hdr, stale, w.n, 0);
+  hipLaunchKernelGGL(k_vor_check<false>, dim3(nb), dim3(kBlock), 0, s, x, y, w, dmax, ring, deg, stale, nullptr, 0);
+  hipLaunchKernelGGL(k_vor_total, dim3(1), dim3(kBlock), 0, s, w, nb, nfail, 0);
   return hipGetLastError();
 }
 
 hipError_t launch_voronoi_update(const DevWs& w, const int32_t* x, const int32_t* y, int dmax,
                                  int32_t* ring, int32_t* deg, uint8_t* stale, int32_t* nfail, int rounds,
                                  hipStream_t s) {
-  const int nb = (w.n + kBlock - 1) / kBlock;
+  const dim3 grid((w.n + kBlock - 1) / kBlock), block(kBlock);
   const bool strips = vor_strips_fit(w);
   const uint32_t* failed = &w.hdr->nvfail;
-  hipError_t e = hipSuccess;
-  for (int r = 0; r < rounds && e == hipSuccess; ++r) {
-    e = launch_voronoi_check(w, x, y, dmax, ring, deg, stale, r == 0 ? nfail : nullptr, s);
-    if (e != hipSuccess) break;
-    hipLaunchKernelGGL(k_vor_sweep, dim3(nb), dim3(kBlock), 0, s, w, x, y, dmax, ring, deg, stale, strips ? 0 : 1);
-    if (strips) launch_vor_strips(w, dmax, ring, deg, stale, failed, s);
-    e = launch_general(w, dmax, ring, deg, false, strips, nullptr, s);
+  // rounds of check and recomputation, then the final certificate: anything
+  // still stale and every row is built again; after a round in which no row
+  // failed the rest does nothing
+  for (int r = 0; r <= rounds; ++r) {
+    const int again = r > 0 ? 1 : 0;
+    hipLaunchKernelGGL(k_vor_clear, grid, block, 0, s, w.hdr, stale, w.n, again);
+    hipLaunchKernelGGL(k_vor_check<true>, grid, block, 0, s, x, y, w, dmax, ring, deg, stale, w.rank, again);
+    hipLaunchKernelGGL(k_vor_total, dim3(1), block, 0, s, w, static_cast<int>(grid.x), again ? nullptr : nfail, again);
+    const bool last = r == rounds;
+    if (!last) {
+      hipLaunchKernelGGL(k_vor_sweep, grid, block, 0, s, w, dmax, ring, deg, stale, w.rank, again);
+      if (!strips) hipLaunchKernelGGL(k_vor_list, grid, block, 0, s, w, stale, again);
+    }
+    if (strips) launch_vor_strips(w, dmax, ring, deg, last ? nullptr : stale, failed, s);
+    const hipError_t e = launch_general(w, dmax, ring, deg, last && !strips, strips, last && !strips ? failed : nullptr, s);
+    if (e != hipSuccess) return e;
   }
-  if (e != hipSuccess) return e;
-  // final certificate; anything still stale: every row again
-  e = launch_voronoi_check(w, x, y, dmax, ring, deg, stale, rounds == 0 ? nfail : nullptr, s);
-  if (e != hipSuccess) return e;
-  if (strips) launch_vor_strips(w, dmax, ring, deg, nullptr, failed, s);
-  return launch_general(w, dmax, ring, deg, !strips, strips, strips ? nullptr : failed, s);
+  return hipSuccess;
 }
 
 }  // namespace nm

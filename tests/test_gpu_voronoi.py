@@ -253,6 +253,42 @@ def test_reuse_test_and_update(step, coincide):
     assert _rows_of(ring.cpu().numpy(), deg.cpu().numpy()) == ref1
 
 
+# Rows held in registers (up to 12 entries, rows of 12 or more) and rows walked
+# by index; no row failing, a few, and most of them; both in the cells' order
+# (the update) and in the caller's (the check alone).
+@pytest.mark.parametrize("kind,dmax,move", [("lattice", 11, 0), ("lattice", 12, 0), ("lattice", 11, 40), ("lattice", 12, 40),
+                                            ("lattice", 64, 400), ("ring", 64, 0), ("ring", 64, 20), ("pairs", 16, 30)])
+def test_update_short_long_and_shared_rows(kind, dmax, move):
+    box, w = 1 << 16, 1 << 11
+    rng = np.random.default_rng(dmax + move)
+    if kind == "ring":
+        x, y = _ring_of(40, box)
+    else:
+        m, a = 32, box // 32
+        i = np.arange(m * m)
+        x = (i % m) * a + (i // m % 2) * (a // 2) + rng.integers(-60, 61, m * m)
+        y = (i // m) * a + rng.integers(-60, 61, m * m)
+        if kind == "pairs":
+            x[[5, 300, 301]], y[[5, 300, 301]] = x[[700, 900, 900]], y[[700, 900, 900]]
+    n = len(x)
+    x, y = x.astype(np.int64) % box, y.astype(np.int64) % box
+    # a turn of every row's start comes with the common shift, failures with the rest
+    x1 = ((x + 3 + rng.integers(-move, move + 1, n)) % box).astype(np.int32)
+    y1 = ((y - 2 + rng.integers(-move, move + 1, n)) % box).astype(np.int32)
+    if kind == "pairs":  # they move together
+        x1[[5, 300, 301]], y1[[5, 300, 301]] = x1[[700, 900, 900]], y1[[700, 900, 900]]
+    x, y = x.astype(np.int32), y.astype(np.int32)
+    ring, deg, st, ws = _gpu_rows(x, y, box, w, dmax=dmax)
+    assert st == 0
+    R, D, X1, Y1 = _dev(ring, torch.int32), _dev(deg, torch.int32), _dev(x1, torch.int32), _dev(y1, torch.int32)
+    alone = int(nm.voronoi_check(ws, X1, Y1, R, D)[1].item())
+    nm.build_cells(ws, X1, Y1)
+    nfail = int(nm.voronoi_update(ws, X1, Y1, R, D).item())
+    assert nm.check(ws) == 0 and nfail == alone
+    assert move > 0 or nfail == 0
+    assert _rows_of(R.cpu().numpy(), D.cpu().numpy()) == _oracle_rows(x1, y1, box)
+
+
 def test_update_from_unrelated_rows():
     n, box, w = 4097, 1 << 16, 1024
     xa, ya, _ = workloads.uniform(n, box=box, seed_pos=81)
