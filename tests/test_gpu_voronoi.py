@@ -369,6 +369,38 @@ def test_voronoi_forces_match_oracle(kind, n, box, w):
         assert np.abs(v[..., c][sel] - ref[key]).max() <= tol
 
 
+# Rows on both sides of the eight lanes that share a particle and of the rows
+# read whole, and rows too narrow for that; the same bits in every order.
+@pytest.mark.parametrize("m,dmax", [(6, 7), (7, 16), (8, 16), (9, 16), (15, 16), (17, 64), (40, 64)])
+def test_voronoi_forces_rows_around_the_lane_group(m, dmax):
+    box, w = 1 << 14, 1 << 9
+    if dmax < 8:  # the centred lattice, a little out of place: six neighbours each
+        i = np.arange(32 * 32)
+        rng = np.random.default_rng(3)
+        x = ((i % 32) * 512 + (i // 32 % 2) * 256 + rng.integers(-20, 21, len(i))) % box
+        y = ((i // 32) * 512 + rng.integers(-20, 21, len(i))) % box
+        x, y = x.astype(np.int32), y.astype(np.int32)
+    else:
+        x, y = _ring_of(m, box)
+    n = len(x)
+    ring, deg, st, ws = _gpu_rows(x, y, box, w, dmax=dmax)
+    assert st == 0 and m in deg
+    off, idx = oracle.voronoi(x, y, box)
+    a = _vm_args(n, box)
+    ref = oracle.voronoi_forces(x, y, box, off, idx, **a)
+    args = (_dev(x, torch.int32), _dev(y, torch.int32), box, _dev(ring, torch.int32), _dev(deg, torch.int32))
+    other = nm.Workspace(n + 1, box, w)
+    got = [nm.voronoi_forces(*args, ws=q, **a) for q in (ws, None, other)]
+    assert nm.check(ws) == 0 and nm.check(other) == 0
+    for k in ("area", "perim", "fx", "fy", "energy"):
+        assert torch.equal(got[0][k], got[1][k]) and torch.equal(got[0][k], got[2][k])
+    scale = _force_scale(a)
+    assert np.allclose(got[0]["area"].cpu().numpy(), ref["area"], rtol=1e-12, atol=0)
+    assert np.allclose(got[0]["perim"].cpu().numpy(), ref["perim"], rtol=1e-12, atol=0)
+    assert np.abs(got[0]["fx"].cpu().numpy() - ref["fx"]).max() <= 1e-9 * scale
+    assert np.abs(got[0]["fy"].cpu().numpy() - ref["fy"]).max() <= 1e-9 * scale
+
+
 def test_voronoi_forces_vanish_on_the_centred_lattice():
     m, box = 16, 1 << 20
     a = box // m
