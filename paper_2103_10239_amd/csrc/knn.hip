@@ -67,43 +67,28 @@ __device__ __forceinline__ bool knn_exact(const DevWs& w, int s, int qx, int qy,
   return top.worst() != ~0ull;
 }
 
-// Reorder the k neighbour slots by exact (d^2, index): used when two of them
-// share a distance field of the 32-bit keys (rare).
-template <int KMAX>
-__device__ __forceinline__ void sort_exact(const DevWs& w, int qx, int qy, int k, int (&slot)[KMAX]) {
-  const int sh = 32 - w.log2_box;
-  unsigned long long kk[KMAX];
+// Reorder neighbours whose distance fields tie (or lie too close for their
+// order to be certain) by the exact (d^2, index): bit t of `link` says that
+// entries t and t + 1 do, the linked runs are sorted by passes of exchanges
+// between linked entries.  exact(v) gives an entry's 64-bit key.  Runs of two
+// are the rule, so no key outside a run is ever formed (sorting all k by 64-bit
+// keys held 64 registers at k = 32).
+template <int KMAX, class Exact>
+__device__ __forceinline__ void sort_linked(uint32_t link, int (&v)[KMAX], Exact&& exact) {
+  bool again = true;
+  while (again) {
+    again = false;
 #pragma unroll
-  for (int t = 0; t < KMAX; ++t) {
-    kk[t] = ~0ull;
-    if (t >= KMAX - k) {
-      const int4 e = w.sorted[slot[t]];
-      const int ex = wrap_axis(e.x - qx, sh), ey = wrap_axis(e.y - qy, sh);
-      kk[t] = pack_key(static_cast<long long>(ex) * ex + static_cast<long long>(ey) * ey, e.z);
+    for (int t = 0; t + 1 < KMAX; ++t) {
+      if ((link >> t) & 1u) {
+        if (exact(v[t + 1]) < exact(v[t])) {
+          const int s = v[t];
+          v[t] = v[t + 1];
+          v[t + 1] = s;
+          again = true;
+        }
+      }
     }
-  }
-  // insertion sort over the static positions (the unused prefix holds ~0)
-#pragma unroll
-  for (int i = 1; i < KMAX; ++i) {
-#pragma unroll
-    for (int j = i; j > 0; --j) {
-      const bool swap = kk[j] < kk[j - 1];
-      const unsigned long long a = kk[j - 1], c = kk[j];
-      const int sa = slot[j - 1], sc = slot[j];
-      kk[j - 1] = swap ? c : a;
-      kk[j] = swap ? a : c;
-      slot[j - 1] = swap ? sc : sa;
-      slot[j] = swap ? sa : sc;
-    }
-  }
-  // the ~0 entries of the unused prefix sorted to the end: rotate them back
-  if (k < KMAX) {
-    int tmp[KMAX];
-#pragma unroll
-    for (int t = 0; t < KMAX; ++t) tmp[t] = slot[t];
-#pragma unroll
-    for (int t = 0; t < KMAX; ++t)
-      if (t >= KMAX - k) slot[t] = tmp[t - (KMAX - k)];
   }
 }
 
@@ -117,31 +102,6 @@ __device__ __forceinline__ long long staged_d2(const int* lpos, int i, int pq, i
     return dx * dx + dy * dy;
   }
   return rel_d2(lpos[i], pq);
-}
-
-// sort_exact for staged neighbours (LDS indices), from the staged positions
-// and particle indices.
-template <int KMAX, bool kWide>
-__device__ __forceinline__ void sort_exact_lds(const int* lpos, const int* lidx, int pq, int pqy, int k,
-                                               int (&lds)[KMAX]) {
-  unsigned long long kk[KMAX];
-#pragma unroll
-  for (int t = 0; t < KMAX; ++t)
-    kk[t] = t >= KMAX - k ? pack_key(staged_d2<kWide>(lpos, lds[t], pq, pqy), lidx[lds[t]]) : 0ull;
-  // the unused prefix holds 0, below every real key, so it stays in front
-#pragma unroll
-  for (int i = 1; i < KMAX; ++i) {
-#pragma unroll
-    for (int j = i; j > 0; --j) {
-      const bool swap = kk[j] < kk[j - 1];
-      const unsigned long long a = kk[j - 1], c = kk[j];
-      const int sa = lds[j - 1], sc = lds[j];
-      kk[j - 1] = swap ? c : a;
-      kk[j] = swap ? a : c;
-      lds[j - 1] = swap ? sc : sa;
-      lds[j] = swap ? sa : sc;
-    }
-  }
 }
 
 // Block side for a query: its edge should sit `reach` mean k-th-neighbour
@@ -199,10 +159,10 @@ __device__ __forceinline__ bool knn_fast(const DevWs& w, const FastCfg& f, int s
     // The k nearest form the set {d^2 >> sh <= that of the k-th} only if the
     // (k+1)-th has a larger distance field; otherwise the exact search decides.
     if (key32_d(kth) >= key32_d(key[KT - 1])) return false;
-    bool tied = false;
+    uint32_t link = 0u;
 #pragma unroll
     for (int t = 0; t < KT - 2; ++t)
-      if (t >= KT - (k + 1)) tied = tied || (key32_d(key[t]) == key32_d(key[t + 1]));
+      if (t >= KT - (k + 1) && key32_d(key[t]) == key32_d(key[t + 1])) link |= 1u << t;
     bool mapped = true;
 #pragma unroll
     for (int t = 0; t < KMAX; ++t) {
@@ -211,7 +171,14 @@ __device__ __forceinline__ bool knn_fast(const DevWs& w, const FastCfg& f, int s
         mapped = mapped && static_cast<uint32_t>(slot[t]) < static_cast<uint32_t>(total);
       }
     }
-    if (mapped && tied) sort_exact<KMAX>(w, qx, qy, k, slot);
+    if (mapped && link != 0u) {
+      const int shx = 32 - w.log2_box;
+      sort_linked<KMAX>(link, slot, [&](int q) {
+        const int4 e = w.sorted[q];
+        const long long ex = wrap_axis(e.x - qx, shx), ey = wrap_axis(e.y - qy, shx);
+        return pack_key(ex * ex + ey * ey, e.z);
+      });
+    }
     return mapped;
   }
   return false;
@@ -297,6 +264,15 @@ __device__ __forceinline__ void finish_query(const DevWs& w, int s, const int4& 
 // ---------------------------------------------------------------------------
 constexpr int kDeferCap = 128;    // uncertified queries listed in LDS per strip
 constexpr double kReachX = 1.25;  // strip half width, in mean k-th-neighbour radii
+// A system stepped by itself with few strips waits for its last uncertified
+// query (9 of 25 us at 1000 particles), so its blocks cover more of the k-th
+// distance's tail where 1.25 radii round to a halo just as wide: n = 1000 and
+// 4000 at k = 7 26 -> 16 us, 16,000 27 -> 24; at 50,000 the candidates cost
+// more (32 -> 34 us), at 10^6 173 -> 185.
+constexpr double kReachXSmall = 1.5;
+constexpr float kReachSmall = 1.6f;
+constexpr int kSmallN = 1 << 14;
+constexpr double kStripQ = 256.0;  // queries per strip
 constexpr double kReachY = 1.2;   // halo height over the expected block height
 
 
@@ -454,14 +430,15 @@ __device__ __forceinline__ bool strip_search(const DevWs& w, const TileCfg& tc, 
       return false;
     }
     if (key32_d(kth) + M >= key32_d(key[KT - 1])) return false;
-    bool tied = false;
+    uint32_t link = 0u;
 #pragma unroll
     for (int t = 0; t < KT - 2; ++t)
-      if (t >= KT - (k + 1)) tied = tied || (key32_d(key[t + 1]) - key32_d(key[t]) <= M);
+      if (t >= KT - (k + 1) && key32_d(key[t + 1]) - key32_d(key[t]) <= M) link |= 1u << t;
 #pragma unroll
     for (int t = 0; t < KMAX; ++t)
       if (t >= KMAX - k) lds[t] = static_cast<int>(key[t] & 0x1FFFu);
-    if (tied) sort_exact_lds<KMAX, kWide>(lpos, lidx, pq, pqy, k, lds);
+    if (link != 0u)
+      sort_linked<KMAX>(link, lds, [&](int i) { return pack_key(staged_d2<kWide>(lpos, i, pq, pqy), lidx[i]); });
     return true;
   }
   return false;
@@ -926,12 +903,14 @@ __device__ __forceinline__ void knn_tile_body(const DevWs& w, const FastCfg& f, 
 
 // Waves per SIMD asked of the compiler: five for the short lists (96 VGPRs,
 // which the LDS of a strip also allows), four for KMAX 12-20, whose insertion
-// networks would otherwise take the kernel to three or two; the spills these
-// limits add (cold for k <= 12) cost less than the waves they gain.  The
+// networks would otherwise take the kernel to three or two, three for KMAX 24
+// and 32 (k = 31, 200,000 uniform particles: 250 us at the one wave it would
+// take, 184 at two, 165 at three, 204 at four); the spills these limits add
+// lie outside the search loops and cost less than the waves they gain.  The
 // batched kernel, which also holds its system's descriptors, spills at five
 // and takes four.
 template <int KMAX>
-constexpr int kKnnWaves = (KMAX >= 12 && KMAX <= 20) ? 4 : (KMAX <= 8 ? 5 : 1);
+constexpr int kKnnWaves = (KMAX >= 12 && KMAX <= 20) ? 4 : (KMAX <= 8 ? 5 : 3);
 template <int KMAX>
 constexpr int kBatchKnnWaves = KMAX <= 8 ? 4 : kKnnWaves<KMAX>;
 
@@ -1009,12 +988,25 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kBatchKn
   }
 }
 
+// Queries per strip of a system run by itself: fewer where 256 would leave
+// CUs without a strip (n = 16,000, k = 7: 32 us with 256, 26 with 64; 50,000,
+// k = 12: 41 and 32; 130,000: 49 with 256, 41 with 128, 58 with 64; larger
+// systems fill the device and stage less with 256, and up to some 4000
+// particles the few strips take one strip's latency whatever their size).
+inline double solo_strip_queries(int n) {
+  return n < 4096 ? kStripQ : (n < 100000 ? 64.0 : (n < 262144 ? 128.0 : kStripQ));
+}
+
 // Strip geometry.  Block rows: up to the expected block height plus one
 // widening step (hy); block width: all W = tw + 2 hx columns, hx the expected
 // half width.  The strip height aims at about 256 queries; the halo must fit
 // the staging buffer and the row table, W <= G (a block never meets itself
 // around the box), and narrow strips keep every block under 2^15 units.
-TileCfg tile_cfg_impl(const DevWs& w, const FastCfg& f, int k, bool narrow_strips) {
+// `queries`: per strip; `reach_x`: half width in mean k-th-neighbour radii;
+// `solo`: a system run by itself.
+TileCfg tile_cfg_impl(const DevWs& w, const FastCfg& f, int k, bool narrow_strips, bool solo = false,
+                      double reach_x = kReachX) {
+  const double queries = solo ? solo_strip_queries(w.n) : kStripQ;
   TileCfg t{1, 1, 0, 0, w.G, w.G, 0, 0};
   const double rho = static_cast<double>(w.n) / static_cast<double>(w.C);  // particles per cell
   const double rr = rho > 1e-12 ? rho : 1e-12;
@@ -1039,7 +1031,7 @@ TileCfg tile_cfg_impl(const DevWs& w, const FastCfg& f, int k, bool narrow_strip
   int hy = min((bq + 2) / 2, 15);  // (hy <= 15: block heights fit 5 bits)
   // The block width is fixed per strip, so it covers the tail of the k-th
   // neighbour distance, not only its mean.
-  int hx = min(max(1, static_cast<int>(ceil(kReachX * rk))), 15);
+  int hx = min(max(1, static_cast<int>(ceil(reach_x * rk))), 15);
   if (f.bfix > 0) hx = min(max(hx, f.bfix / 2), 15);
   // Strip width: wider as the halo widens (hx 2: two columns, hx >= 3: four,
   // or two for lists of up to 8, where a block's candidates (its rows times
@@ -1052,7 +1044,18 @@ TileCfg tile_cfg_impl(const DevWs& w, const FastCfg& f, int k, bool narrow_strip
   // sub-strip kernel, whose larger halos overflow LDS more often, and the
   // field-of-view lists, whose blocks span every column of the strip.
   int tw = narrow_strips ? (hx >= 3 ? 2 : 1) : (hx >= 3 ? (k <= 8 ? 2 : 4) : (hx >= 2 ? 2 : 1));
-  while (tw < 16 && 2 * tw <= w.G && 256.0 / (tw * rr) > 1.1 * (kTwRows - 2 * hy)) tw *= 2;
+  auto widen = [&]() {
+    while (tw < 16 && 2 * tw <= w.G && kStripQ / (tw * rr) > 1.1 * (kTwRows - 2 * hy)) tw *= 2;
+  };
+  widen();
+  // Sparse systems, whose blocks would span 2^15 units, take one column where
+  // the rows allow: their buffer holds half the particles, and one column may
+  // bring the block under the limit (k = 31, 200,000 particles: 626 -> 490 us
+  // clustered, 170 -> 163 uniform; k = 12, 50,000: 41 -> 33).
+  if (solo && (static_cast<long long>(tw + 2 * hx) << w.log2_w) >= 32768) {
+    tw = 1;
+    widen();
+  }
   while (hx > 1 && tw + 2 * hx > w.G) --hx;
   while (hy > 1 && 2 * hy + 1 > w.G) --hy;
   if (tw + 2 * hx > w.G || 2 * hy + 1 > w.G) return plain();
@@ -1060,7 +1063,7 @@ TileCfg tile_cfg_impl(const DevWs& w, const FastCfg& f, int k, bool narrow_strip
   const bool narrow = (static_cast<long long>(W) << w.log2_w) < 32768 &&
                       (static_cast<long long>(2 * hy + 1) << w.log2_w) < 32768;
   const int cap = narrow ? kStripPts : kStripPts / 2;
-  int th = static_cast<int>(ceil(256.0 / (tw * rr)));
+  int th = static_cast<int>(ceil(queries / (tw * rr)));
   th = max(1, min(th, w.G));
   while (th > 1 && (th + 2 * hy > kStripRows || (th + 2 * hy) * W * rho > 0.75 * cap)) --th;
   if (th + 2 * hy > kStripRows) return plain();
@@ -1075,10 +1078,21 @@ TileCfg tile_cfg_impl(const DevWs& w, const FastCfg& f, int k, bool narrow_strip
   return t;
 }
 
+// The strips of a system run by itself (f.reach too may grow for small ones).
+TileCfg solo_cfg(const DevWs& w, FastCfg& f, int k) {
+  const TileCfg t = tile_cfg_impl(w, f, k, f.split != 0, true);
+  // (the sub-strip kernel takes each strip's halo from its own density)
+  if (w.n > kSmallN || f.bfix > 0 || f.split != 0 || t.hx == 0) return t;
+  const TileCfg wider = tile_cfg_impl(w, f, k, f.split != 0, true, kReachXSmall);
+  if (wider.hx <= t.hx) return t;
+  f.reach = kReachSmall;
+  return tile_cfg_impl(w, f, k, f.split != 0, true, kReachXSmall);
+}
+
 template <int KMAX, bool kAlign>
-hipError_t launch_t(const DevWs& w, const FastCfg& f, int k, int32_t* nbr, long long* d2,
+hipError_t launch_t(const DevWs& w, FastCfg f, int k, int32_t* nbr, long long* d2,
                     const AlignArgs& a, hipStream_t s) {
-  const TileCfg tc = tile_cfg_impl(w, f, k, f.split != 0);
+  const TileCfg tc = solo_cfg(w, f, k);
   const int ntiles = tc.ntx * tc.nty;
   if (f.split && tc.hx > 0)
     hipLaunchKernelGGL((k_knn<KMAX, kAlign, kOverflowSplit>), dim3(ntiles), dim3(kBlock), 0, s, w, f,
@@ -1167,7 +1181,7 @@ hipError_t launch_knn_fov_strips(const DevWs& w, int block, const float* theta, 
   const double alpha = acos(fmax(-1.0, fmin(1.0, c / 4096.0)));
   const double frac = fmax(alpha / 3.141592653589793, 1.0 / 64.0);
   const int ks = static_cast<int>(ceil(k / frac));
-  const TileCfg tc = tile_cfg_impl(w, f, ks, true);
+  const TileCfg tc = tile_cfg_impl(w, f, ks, true, true);
   f.reach = static_cast<float>(f.reach * sqrt(static_cast<double>(ks) / k));
   AlignArgs a{};
   a.theta = theta;
@@ -1181,8 +1195,8 @@ hipError_t launch_knn_fov_strips(const DevWs& w, int block, const float* theta, 
 }
 
 void knn_layout(const DevWs& w, int k, int block, int32_t out[10]) {
-  const FastCfg f = fast_cfg(w, k, block);
-  const TileCfg tc = tile_cfg_impl(w, f, k, f.split != 0);
+  FastCfg f = fast_cfg(w, k, block);
+  const TileCfg tc = solo_cfg(w, f, k);
   // kernel: 0 = one row of queries per strip, searched in global memory;
   // 1 = staged strips (default kernel); 2 = staged strips, sub-strip kernel
   out[0] = tc.hx == 0 ? 0 : (f.split ? 2 : 1);

@@ -829,3 +829,37 @@ def test_knn_fov_after_fused_binning():
     ref, ok = oracle.knn_fov(x, y, th, L, k, 1000)
     assert ok and nm.check(ws) == 0
     assert np.array_equal(got.cpu().numpy(), ref)
+
+
+# Strips of a system run by itself: queries per strip (n = 100,000, 262,144),
+# wider halos of small systems (n = 2^14), one column where blocks would span
+# 2^15 units; runs of near ties sorted entry by entry in every list size.
+@pytest.mark.parametrize("n,k,w", [(1000, 7, 1 << 16), (4001, 7, 1 << 15), (16384, 7, 1 << 14), (16385, 7, 1 << 14),
+                                   (3001, 31, 1 << 15), (12001, 24, 1 << 13)])
+def test_knn_solo_strips_match_oracle(n, k, w):
+    x, y, _ = _gen("uniform", n)
+    nbr, d2 = _gpu_knn_block(x, y, k, w, 0)
+    rn, rd = oracle.knn(x, y, L, k)
+    assert np.array_equal(nbr, rn) and np.array_equal(d2, rd)
+
+
+@pytest.mark.parametrize("n", [99999, 100000, 262143, 262144])
+@pytest.mark.parametrize("kind,k", [("uniform", 7), ("uniform", 31), ("clustered", 20)])
+def test_knn_solo_strips_match_ring_search(n, kind, k):
+    x, y, _ = _gen(kind, n)
+    w = nm.suggest_cell_w(n, L)
+    nbr, d2 = _gpu_knn_block(x, y, k, w, 0)
+    rn, rd = _gpu_knn_block(x, y, k, w, -1)
+    assert np.array_equal(nbr, rn) and np.array_equal(d2, rd)
+
+
+@pytest.mark.parametrize("k", [16, 20, 24, 32])
+@pytest.mark.parametrize("block", [0, nm.NM_BLOCK_SUBSTRIPS])
+def test_knn_runs_of_near_ties_long_lists(k, block):
+    x, y, a = workloads.lattice(64)
+    rng = np.random.default_rng(6)
+    x = ((x.astype(np.int64) + rng.integers(-2, 3, x.size)) % L).astype(np.int32)
+    y = ((y.astype(np.int64) + rng.integers(-2, 3, y.size)) % L).astype(np.int32)
+    nbr, d2 = _gpu_knn_block(x, y, k, a, block)
+    rn, rd = oracle.knn(x, y, L, k)
+    assert np.array_equal(nbr, rn) and np.array_equal(d2, rd)
