@@ -48,6 +48,7 @@ __device__ __forceinline__ void ws_init_body(const DevWs& w, int b, int nb) {
         w.hdr->ndefer[ph] = 0u;
         w.hdr->nchunk[ph] = 0u;
       }
+      w.hdr->nmdone = 0u;
       w.hdr->nvwide = 0u;
       w.hdr->nvdone = 0u;
       w.hdr->nvstale = 0u;

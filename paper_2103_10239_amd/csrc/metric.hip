@@ -122,7 +122,7 @@ constexpr int kWaveKeys = 512;    // longest row a wave sorts in LDS
 constexpr int kWaves = kBlock / 64;
 constexpr int kChunkQ = 512;      // queries per chunk of a split strip
 constexpr int kMaxChunks = 256;   // chunks one strip may be split into
-constexpr int kChunkGrid = 1024;  // workgroups of the chunk kernels
+constexpr int kChunkGrid = 1024;  // workgroups of the follow-up kernels
 
 // Wave-scope ordering of LDS accesses between the lanes of one wave.
 __device__ __forceinline__ void wave_sync() {
@@ -180,7 +180,7 @@ struct StripShared {
   uint8_t rowid[kStripPts];
   int4 chunk[kMaxChunks];  // this strip's chunks: {tile, r0 | r1 << 16 | unstaged << 30, qa, qb}
   int heavy[kChunkQ];      // queries of the current batch left to the waves
-  int nchunk, nlocal, nheavy, nlane;
+  int nchunk, nall, nlocal, nheavy, nlane;
 };
 
 // Strip of tile `tile` as a strip geometry, rows [r0, r1) of it.
@@ -278,9 +278,8 @@ __device__ __forceinline__ StripLds strip_lds(StripShared& S) {
 template <class Op>
 __device__ __forceinline__ void run_chunk(const DevWs& w, const MetricCfg& mc, StripShared& S, int4 c,
                                           int total, const Op& op) {
-  const bool unstaged = (c.y >> 30) & 1;
   const int r0 = c.y & 0x1FF, r1 = (c.y >> 16) & 0x1FF;
-  const StripGeo g = tile_geo(w, mc, c.x, r0, r1, !unstaged);
+  const StripGeo g = tile_geo(w, mc, c.x, r0, r1, true);
   int npts, nq;
   // Staging (global reads and barriers) issues first; other strips' searches
   // fill its gaps.
@@ -323,8 +322,10 @@ __device__ __forceinline__ int split_strip(const MetricCfg& mc, StripShared& S, 
 }
 
 // Strip kernels' body: stage tile `tile`; a strip that fits LDS and holds at
-// most kChunkQ queries is run here; otherwise its chunks go to the chunk
-// list (those beyond the list's capacity are run here).
+// most kChunkQ queries is run here; otherwise its staged chunks go to the
+// chunk list (those beyond the list's capacity are run here) and the queries
+// of its unstaged ones to the deferred list, so that both lists are complete
+// when the strip kernel ends and one kernel follows it up.
 template <class Op>
 __device__ __forceinline__ void strip_tile(const DevWs& w, const MetricCfg& mc, int tile, const Op& op) {
   __shared__ StripShared S;
@@ -343,20 +344,62 @@ __device__ __forceinline__ void strip_tile(const DevWs& w, const MetricCfg& mc, 
     return;
   }
   if (threadIdx.x == 0) {
-    const int nc = split_strip(mc, S, tile, ty, cap);
+    // staged chunks first, unstaged ones from the table's end
+    const int all = split_strip(mc, S, tile, ty, cap);
+    int nc = 0, nu = 0;
+    for (int c = 0; c < all - nu;) {
+      const int4 v = S.chunk[c];
+      if ((v.y >> 30) & 1) {
+        ++nu;
+        S.chunk[c] = S.chunk[all - nu];
+        S.chunk[all - nu] = v;
+      } else {
+        ++c;
+        ++nc;
+      }
+    }
     const uint32_t base = atomicAdd(&w.hdr->nchunk[Op::kPass], static_cast<uint32_t>(nc));
     const int room = base >= static_cast<uint32_t>(w.chunk_cap)
                          ? 0 : min(nc, w.chunk_cap - static_cast<int>(base));
     for (int c = 0; c < room; ++c) w.chunks[base + c] = S.chunk[c];
     S.nchunk = nc;
+    S.nall = all;
     S.nlocal = room;  // chunks [room, nc) did not fit the list
   }
   __syncthreads();
-  const int nc = S.nchunk;
+  const int nc = S.nchunk, all = S.nall;
+  // (the row tables are still the whole strip's: query numbers count from its
+  // first row, an unstaged chunk holds whole rows)
+  for (int c = nc; c < all; ++c) {
+    const int r0 = S.chunk[c].y & 0x1FF, r1 = (S.chunk[c].y >> 16) & 0x1FF;
+    run_queries(w, mc, S, geo, false, S.qoff[r0], S.qoff[r1], op);
+  }
+  __syncthreads();
   for (int c = S.nlocal; c < nc; ++c) run_chunk(w, mc, S, S.chunk[c], total, op);
 }
 
-// Chunk kernels' body: the workgroups take the listed chunks in turn.
+// Follow-up kernels, after the strip kernel of their pass: the workgroups take
+// the listed chunks in turn, then their waves the deferred rows, and the last
+// workgroup empties both lists.  Both are empty on most systems: nothing is
+// counted then (a count of the workgroups, one atomic each on one address,
+// took 10 us; a kernel that reset the lists at the start of every call and
+// separate chunk and wave kernels took three more launches a call).
+__device__ __forceinline__ bool nothing_listed(const DevWs& w, int ph) {
+  return w.hdr->nchunk[ph] == 0u && w.hdr->ndefer[ph] == 0u;
+}
+
+__device__ __forceinline__ void empty_lists(const DevWs& w, int ph) {
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    __threadfence();
+    if (atomicAdd(&w.hdr->nmdone, 1u) == gridDim.x - 1) {
+      w.hdr->nchunk[ph] = 0u;
+      w.hdr->ndefer[ph] = 0u;
+      w.hdr->nmdone = 0u;
+    }
+  }
+}
+
 template <class Op>
 __device__ __forceinline__ void strip_chunks(const DevWs& w, const MetricCfg& mc, const Op& op) {
   __shared__ StripShared S;
@@ -393,19 +436,6 @@ __device__ __forceinline__ void wave_within(const DevWs& w, int s, const int4& q
       f(hit, d2, j);
     }
   });
-}
-
-// Empty both passes' lists and reset the row-length scan; first kernel of
-// every metric-list call.
-__global__ __launch_bounds__(kBlock) void k_metric_reset(DevWs w) {
-  for (int t = threadIdx.x; t < w.nb_scan_m; t += blockDim.x) w.scan_m->flags[t] = 0ull;
-  if (threadIdx.x == 0) {
-    w.scan_m->ticket = 0u;
-    for (int ph = 0; ph < 2; ++ph) {
-      w.hdr->ndefer[ph] = 0u;
-      w.hdr->nchunk[ph] = 0u;
-    }
-  }
 }
 
 // Count pass: row lengths |{j != i : d^2 <= rc2}| into offsets[i].
@@ -460,6 +490,10 @@ struct CountOp {
 
 __global__ __launch_bounds__(kBlock) void k_metric_count(DevWs w, MetricCfg mc, long long rc2,
                                                          int32_t* __restrict__ offsets) {
+  if (blockIdx.x == gridDim.x - 1) {  // reset the row-length scan, two kernels on
+    for (int t = threadIdx.x; t < w.nb_scan_m; t += kBlock) w.scan_m->flags[t] = 0ull;
+    if (threadIdx.x == 0) w.scan_m->ticket = 0u;
+  }
   if (!ws_ready(w)) {
     if (blockIdx.x == 0 && threadIdx.x == 0) set_err(w.hdr, NM_E_INVAL);
     return;
@@ -467,13 +501,10 @@ __global__ __launch_bounds__(kBlock) void k_metric_count(DevWs w, MetricCfg mc, 
   strip_tile(w, mc, xcd_tile(blockIdx.x, gridDim.x), CountOp{offsets, static_cast<unsigned long long>(rc2)});
 }
 
-__global__ __launch_bounds__(kBlock) void k_metric_count_chunks(DevWs w, MetricCfg mc, long long rc2,
-                                                                int32_t* __restrict__ offsets) {
+__global__ __launch_bounds__(kBlock) void k_metric_count_rest(DevWs w, MetricCfg mc, long long rc2,
+                                                              int32_t* __restrict__ offsets) {
+  if (nothing_listed(w, 0)) return;
   strip_chunks(w, mc, CountOp{offsets, static_cast<unsigned long long>(rc2)});
-}
-
-__global__ __launch_bounds__(kBlock) void k_metric_count_waves(DevWs w, long long rc2,
-                                                               int32_t* __restrict__ offsets) {
   const int total = min(w.start[w.C], w.n);
   for_each_deferred(w, 0, [&](int s) {
     const int4 q = w.sorted[s];
@@ -481,6 +512,7 @@ __global__ __launch_bounds__(kBlock) void k_metric_count_waves(DevWs w, long lon
     wave_within(w, s, q, rc2, total, [&](bool hit, long long, int) { cnt += __popcll(__ballot(hit)); });
     if ((threadIdx.x & 63) == 0) offsets[q.z] = cnt;
   });
+  empty_lists(w, 0);
 }
 
 // Rows of the fill: offset and length of a row from its two offsets, checked
@@ -851,22 +883,16 @@ __global__ __launch_bounds__(kBlock) void k_metric_fill(DevWs w, MetricCfg mc, l
   strip_tile(w, mc, xcd_tile(blockIdx.x, gridDim.x), FillOp{offsets, idx, rc2, nnz, key_shift(rc2)});
 }
 
-__global__ __launch_bounds__(kBlock) void k_metric_fill_chunks(DevWs w, MetricCfg mc, long long rc2,
-                                                               const int32_t* __restrict__ offsets,
-                                                               int32_t* __restrict__ idx, long long cap) {
-  const long long nnz = offsets[w.n];
-  if (nnz > cap || nnz < 0) return;  // reported by the strip kernel; the lists are empty
-  strip_chunks(w, mc, FillOp{offsets, idx, rc2, nnz, key_shift(rc2)});
-}
-
-// One wave per deferred row: its keys gathered into LDS by ballot
-// compaction, placed by rank and written out; rows longer than
+// The listed chunks, then one wave per deferred row: its keys gathered into
+// LDS by ballot compaction, placed by rank and written out; rows longer than
 // kWaveKeys take the chunked selection in the wave's first lane.
-__global__ __launch_bounds__(kBlock) void k_metric_fill_waves(DevWs w, long long rc2,
-                                                              const int32_t* __restrict__ offsets,
-                                                              int32_t* __restrict__ idx, long long cap) {
+__global__ __launch_bounds__(kBlock) void k_metric_fill_rest(DevWs w, MetricCfg mc, long long rc2,
+                                                             const int32_t* __restrict__ offsets,
+                                                             int32_t* __restrict__ idx, long long cap) {
+  if (nothing_listed(w, 1)) return;  // (so also where nnz > cap, reported by the strip kernel)
   const long long nnz = offsets[w.n];
-  const bool ok = nnz <= cap && nnz >= 0;  // otherwise the list is empty
+  const bool ok = nnz <= cap && nnz >= 0;
+  strip_chunks(w, mc, FillOp{offsets, idx, rc2, nnz, key_shift(rc2)});
   const int total = min(w.start[w.C], w.n);
   const int lane = threadIdx.x & 63;
   unsigned long long* buf = wave_keys();
@@ -894,20 +920,19 @@ __global__ __launch_bounds__(kBlock) void k_metric_fill_waves(DevWs w, long long
     }
     wave_sort_write(buf, static_cast<int>(m), out);
   });
+  empty_lists(w, 1);
 }
 
-// Grid of the wave kernels: enough waves to spread a deferred list over
-// every CU.
-int wave_grid(const DevWs& w) { return max(1, min(1024, (w.n + kWaves - 1) / kWaves)); }
+// Workgroups of the follow-up kernels: enough waves to spread a deferred list
+// over every CU.
+int rest_grid(const DevWs& w) { return max(1, min(kChunkGrid, (w.n + kWaves - 1) / kWaves)); }
 
 }  // namespace
 
 hipError_t launch_metric_count(const DevWs& w, long long rc2, int32_t* offsets, hipStream_t s) {
   const MetricCfg mc = metric_cfg(w, rc2);
-  hipLaunchKernelGGL(k_metric_reset, dim3(1), dim3(kBlock), 0, s, w);
   hipLaunchKernelGGL(k_metric_count, dim3(mc.ntx * mc.nty), dim3(kBlock), 0, s, w, mc, rc2, offsets);
-  hipLaunchKernelGGL(k_metric_count_chunks, dim3(kChunkGrid), dim3(kBlock), 0, s, w, mc, rc2, offsets);
-  hipLaunchKernelGGL(k_metric_count_waves, dim3(wave_grid(w)), dim3(kBlock), 0, s, w, rc2, offsets);
+  hipLaunchKernelGGL(k_metric_count_rest, dim3(rest_grid(w)), dim3(kBlock), 0, s, w, mc, rc2, offsets);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_scan_rows(offsets, w.n, w.scan_m, w.nb_scan_m, w.hdr, s);
@@ -918,10 +943,8 @@ hipError_t launch_metric_fill(const DevWs& w, long long rc2, const int32_t* offs
   const MetricCfg mc = metric_cfg(w, rc2);
   hipLaunchKernelGGL(k_metric_fill, dim3(mc.ntx * mc.nty), dim3(kBlock), 0, s, w, mc, rc2, offsets,
                      idx, cap);
-  hipLaunchKernelGGL(k_metric_fill_chunks, dim3(kChunkGrid), dim3(kBlock), 0, s, w, mc, rc2, offsets,
+  hipLaunchKernelGGL(k_metric_fill_rest, dim3(rest_grid(w)), dim3(kBlock), 0, s, w, mc, rc2, offsets,
                      idx, cap);
-  hipLaunchKernelGGL(k_metric_fill_waves, dim3(wave_grid(w)), dim3(kBlock), 0, s, w, rc2, offsets, idx,
-                     cap);
   return hipGetLastError();
 }
 

@@ -52,14 +52,14 @@ struct WsHeader {
   int32_t err;
   int32_t n, box, cell_w;
   uint32_t built;
-  uint32_t ndefer[2];  // metric rows deferred to the wave kernels (count, fill pass)
-  uint32_t nchunk[2];  // metric strip chunks pushed to the chunk kernels (count, fill pass)
+  uint32_t ndefer[2];  // metric rows deferred to the waves of the follow-up kernel (count, fill pass)
+  uint32_t nchunk[2];  // metric strip chunks pushed to it (count, fill pass)
   uint32_t nvwide;     // Voronoi cells listed for the 64-bit kernel (in vlist)
   uint32_t nvdone;     // workgroups of that kernel finished (the last one empties the list)
   uint32_t nvstale;    // Voronoi rows listed for the general kernel (in rank)
   uint32_t nvfail;     // particles whose Voronoi row failed the last reuse test
   uint32_t nvgo;       // rows failed in the update's last reuse test
-  int32_t pad0;
+  uint32_t nmdone;     // workgroups of a metric follow-up kernel finished
   int64_t off_start;   // bytes from here to start and sorted, for calls that get
   int64_t off_sorted;  // the workspace without its grid
   int32_t pad[44];

@@ -863,3 +863,22 @@ def test_knn_runs_of_near_ties_long_lists(k, block):
     nbr, d2 = _gpu_knn_block(x, y, k, a, block)
     rn, rd = oracle.knn(x, y, L, k)
     assert np.array_equal(nbr, rn) and np.array_equal(d2, rd)
+
+
+def test_metric_lists_one_workspace_many_calls():
+    # The lists of chunks and deferred rows are emptied by the kernel that runs
+    # them: calls with staged chunks, with rows too dense to stage, with neither
+    # and with too little room follow each other on one workspace.
+    x, y = _dense_patch(3000, 1000, 2000, 5)
+    w = 1024
+    ws = nm.Workspace(len(x), L, w)
+    X, Y = _dev(x, torch.int32), _dev(y, torch.int32)
+    nm.build_cells(ws, X, Y)
+    for rc in (100, 10, 3000, 100, 0, 900, 100):
+        small = torch.empty(1, dtype=torch.int32, device="cuda")
+        nm.metric_list(ws, rc ** 2, idx=small)
+        assert nm.check(ws) == nm.NM_E_CAPACITY
+        offs, idx = nm.metric_list(ws, rc ** 2)
+        assert nm.check(ws) == 0
+        ro, ri, _ = oracle.metric_list(x, y, L, rc ** 2)
+        assert np.array_equal(offs.cpu().numpy(), ro) and np.array_equal(idx.cpu().numpy(), ri)
