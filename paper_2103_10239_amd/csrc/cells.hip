@@ -48,7 +48,6 @@ __device__ __forceinline__ void ws_init_body(const DevWs& w, int b, int nb) {
         w.hdr->ndefer[ph] = 0u;
         w.hdr->nchunk[ph] = 0u;
       }
-      w.hdr->nmdone = 0u;
       w.hdr->nvwide = 0u;
       w.hdr->nvdone = 0u;
       w.hdr->nvstale = 0u;
@@ -109,6 +108,10 @@ __device__ __forceinline__ void scan_body(int32_t* in, int32_t* out, int64_t m, 
   if (threadIdx.x == 0) s_tile = atomicAdd(&st->ticket, 1u);
   __syncthreads();
   const uint32_t tile = s_tile;
+  if (tile == 0 && threadIdx.x == 0) {  // (the metric count pass's lists, run before this)
+    hdr->ndefer[0] = 0u;
+    hdr->nchunk[0] = 0u;
+  }
   const int64_t base = static_cast<int64_t>(tile) * kScanTile + threadIdx.x * kScanItems;
 
   int32_t v[kScanItems];

@@ -379,25 +379,14 @@ __device__ __forceinline__ void strip_tile(const DevWs& w, const MetricCfg& mc, 
 }
 
 // Follow-up kernels, after the strip kernel of their pass: the workgroups take
-// the listed chunks in turn, then their waves the deferred rows, and the last
-// workgroup empties both lists.  Both are empty on most systems: nothing is
-// counted then (a count of the workgroups, one atomic each on one address,
-// took 10 us; a kernel that reset the lists at the start of every call and
-// separate chunk and wave kernels took three more launches a call).
+// the listed chunks in turn, then their waves the deferred rows.  Both lists
+// are empty on most systems.  A kernel that runs between two uses of a list
+// empties it: the scan the count pass's, the next count kernel the fill
+// pass's.  (Separate chunk and wave kernels, and one that reset the lists at
+// the start of every call, took three more launches a call; the last
+// workgroup emptying them, one atomic each on one address, 10 us a pass.)
 __device__ __forceinline__ bool nothing_listed(const DevWs& w, int ph) {
   return w.hdr->nchunk[ph] == 0u && w.hdr->ndefer[ph] == 0u;
-}
-
-__device__ __forceinline__ void empty_lists(const DevWs& w, int ph) {
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    __threadfence();
-    if (atomicAdd(&w.hdr->nmdone, 1u) == gridDim.x - 1) {
-      w.hdr->nchunk[ph] = 0u;
-      w.hdr->ndefer[ph] = 0u;
-      w.hdr->nmdone = 0u;
-    }
-  }
 }
 
 template <class Op>
@@ -492,7 +481,11 @@ __global__ __launch_bounds__(kBlock) void k_metric_count(DevWs w, MetricCfg mc, 
                                                          int32_t* __restrict__ offsets) {
   if (blockIdx.x == gridDim.x - 1) {  // reset the row-length scan, two kernels on
     for (int t = threadIdx.x; t < w.nb_scan_m; t += kBlock) w.scan_m->flags[t] = 0ull;
-    if (threadIdx.x == 0) w.scan_m->ticket = 0u;
+    if (threadIdx.x == 0) {
+      w.scan_m->ticket = 0u;
+      w.hdr->ndefer[1] = 0u;  // the last fill's lists
+      w.hdr->nchunk[1] = 0u;
+    }
   }
   if (!ws_ready(w)) {
     if (blockIdx.x == 0 && threadIdx.x == 0) set_err(w.hdr, NM_E_INVAL);
@@ -512,7 +505,6 @@ __global__ __launch_bounds__(kBlock) void k_metric_count_rest(DevWs w, MetricCfg
     wave_within(w, s, q, rc2, total, [&](bool hit, long long, int) { cnt += __popcll(__ballot(hit)); });
     if ((threadIdx.x & 63) == 0) offsets[q.z] = cnt;
   });
-  empty_lists(w, 0);
 }
 
 // Rows of the fill: offset and length of a row from its two offsets, checked
@@ -920,7 +912,6 @@ __global__ __launch_bounds__(kBlock) void k_metric_fill_rest(DevWs w, MetricCfg 
     }
     wave_sort_write(buf, static_cast<int>(m), out);
   });
-  empty_lists(w, 1);
 }
 
 // Workgroups of the follow-up kernels: enough waves to spread a deferred list
