@@ -882,3 +882,37 @@ def test_metric_lists_one_workspace_many_calls():
         assert nm.check(ws) == 0
         ro, ri, _ = oracle.metric_list(x, y, L, rc ** 2)
         assert np.array_equal(offs.cpu().numpy(), ro) and np.array_equal(idx.cpu().numpy(), ri)
+
+
+# One-workgroup binning on both sides of its limits (4096 particles, 4096
+# cells), and prefix sums whose last share is whole or not; the fused step too.
+@pytest.mark.parametrize("n,w", [(2, L), (3, L // 2), (1023, L // 16), (1024, L // 32), (1025, L // 64), (4096, L // 64),
+                                 (4097, L // 64), (4096, L // 128), (2049, L // 128), (5000, L // 2), (5000, L // 256)])
+def test_small_binning_step_matches_oracle(n, w):
+    x, y, th = _gen("uniform", n) if n > 3 else (np.array([5, 9, 5], np.int32)[:n], np.array([1, 2, 1], np.int32)[:n], None)
+    th = workloads.headings(n)
+    k = min(7, n - 1)
+    p = nm.make_params(L, v0=64, eta=0.2, seed=11)
+    sysm = nm.System.create(x, y, th, k, p, cell_w=w)
+    sysm.step()
+    assert nm.check(sysm.ws) == 0
+    rn, rx, ry, rt = oracle.step(x, y, th, L, k, v0=64, eta=0.2, seed=11)
+    assert np.array_equal(sysm.nbr.cpu().numpy(), rn)
+    assert np.array_equal(sysm.x.cpu().numpy(), rx) and np.array_equal(sysm.y.cpu().numpy(), ry)
+    d = np.remainder(sysm.theta.cpu().numpy().astype(np.float64) - rt + np.pi, 2 * np.pi) - np.pi
+    assert np.abs(d).max() <= 1e-5
+
+
+def test_small_binning_leaves_out_what_is_outside_the_box():
+    n = 1000
+    x, y, _ = workloads.uniform(n)
+    x[[3, 500]] = [-1, L]
+    ws = nm.Workspace(n, L, L // 16)
+    nm.build_cells(ws, _dev(x, torch.int32), _dev(y, torch.int32))
+    assert nm.check(ws) == nm.NM_E_RANGE
+    # the rows of the others come from the others
+    nbr, _ = nm.knn(ws, 3)
+    assert nm.check(ws) == 0
+    keep = np.setdiff1d(np.arange(n), [3, 500])
+    rn, _ = oracle.knn(x[keep], y[keep], L, 3)
+    assert np.array_equal(nbr.cpu().numpy()[keep], keep[rn])
