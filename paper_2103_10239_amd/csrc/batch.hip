@@ -62,7 +62,7 @@ BatchSys make_batch_sys(const SysSpec& s, int k) {
   make_layout(&s.g, &lay);
   d.w = dev_ws(&s.g, lay, s.ws);
   d.f = fast_cfg(d.w, k, s.g.block);
-  d.tc = tile_cfg(d.w, d.f, k);
+  d.tc = tile_cfg(d.w, d.f, k, s.use);
   for (int t = 0; t < 2; ++t) {
     d.x[t] = s.x[t];
     d.y[t] = s.y[t];

@@ -25,6 +25,7 @@ struct SysSpec {
   uint32_t sys_id;
   uint64_t step;   // Philox step of the system's next step
   int32_t parity;  // buffer holding its current state
+  StripUse use = kUseBatch;
 };
 
 // Device descriptor of one system for k nearest neighbours.

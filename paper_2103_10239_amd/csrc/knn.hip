@@ -273,6 +273,14 @@ constexpr double kReachXSmall = 1.5;
 constexpr float kReachSmall = 1.6f;
 constexpr int kSmallN = 1 << 14;
 constexpr double kStripQ = 256.0;  // queries per strip
+// Share of the staging buffer that a sparse ("wide") strip of a served job
+// fills at the mean density.  No tuner picks those grids, and a strip over the
+// buffer searches global memory, which the whole iteration waits for: 16 jobs
+// of 1024 to 131,072 particles, half clustered, up to 20 steps: 4.6-15.9 ms at
+// 0.75 (by the clusters), 4.0-4.6 at 0.5, all uniform 3.54 and 3.52, all
+// clustered 9.6 and 5.5.  (Tuned batches keep 0.75: 512 systems of up to 8192
+// particles 303 us against 329.)
+constexpr double kFillServed = 0.5;
 constexpr double kReachY = 1.2;   // halo height over the expected block height
 
 
@@ -1002,11 +1010,10 @@ inline double solo_strip_queries(int n) {
 // half width.  The strip height aims at about 256 queries; the halo must fit
 // the staging buffer and the row table, W <= G (a block never meets itself
 // around the box), and narrow strips keep every block under 2^15 units.
-// `queries`: per strip; `reach_x`: half width in mean k-th-neighbour radii;
-// `solo`: a system run by itself.
-TileCfg tile_cfg_impl(const DevWs& w, const FastCfg& f, int k, bool narrow_strips, bool solo = false,
+// `reach_x`: half width in mean k-th-neighbour radii.
+TileCfg tile_cfg_impl(const DevWs& w, const FastCfg& f, int k, bool narrow_strips, StripUse use = kUseBatch,
                       double reach_x = kReachX) {
-  const double queries = solo ? solo_strip_queries(w.n) : kStripQ;
+  const double queries = use == kUseSolo ? solo_strip_queries(w.n) : kStripQ;
   TileCfg t{1, 1, 0, 0, w.G, w.G, 0, 0};
   const double rho = static_cast<double>(w.n) / static_cast<double>(w.C);  // particles per cell
   const double rr = rho > 1e-12 ? rho : 1e-12;
@@ -1052,7 +1059,7 @@ TileCfg tile_cfg_impl(const DevWs& w, const FastCfg& f, int k, bool narrow_strip
   // the rows allow: their buffer holds half the particles, and one column may
   // bring the block under the limit (k = 31, 200,000 particles: 626 -> 490 us
   // clustered, 170 -> 163 uniform; k = 12, 50,000: 41 -> 33).
-  if (solo && (static_cast<long long>(tw + 2 * hx) << w.log2_w) >= 32768) {
+  if (use == kUseSolo && (static_cast<long long>(tw + 2 * hx) << w.log2_w) >= 32768) {
     tw = 1;
     widen();
   }
@@ -1065,7 +1072,8 @@ TileCfg tile_cfg_impl(const DevWs& w, const FastCfg& f, int k, bool narrow_strip
   const int cap = narrow ? kStripPts : kStripPts / 2;
   int th = static_cast<int>(ceil(queries / (tw * rr)));
   th = max(1, min(th, w.G));
-  while (th > 1 && (th + 2 * hy > kStripRows || (th + 2 * hy) * W * rho > 0.75 * cap)) --th;
+  const double fill = use == kUseServed && !narrow ? kFillServed : 0.75;
+  while (th > 1 && (th + 2 * hy > kStripRows || (th + 2 * hy) * W * rho > fill * cap)) --th;
   if (th + 2 * hy > kStripRows) return plain();
   t.tw = tw;
   t.th = th;
@@ -1080,13 +1088,13 @@ TileCfg tile_cfg_impl(const DevWs& w, const FastCfg& f, int k, bool narrow_strip
 
 // The strips of a system run by itself (f.reach too may grow for small ones).
 TileCfg solo_cfg(const DevWs& w, FastCfg& f, int k) {
-  const TileCfg t = tile_cfg_impl(w, f, k, f.split != 0, true);
+  const TileCfg t = tile_cfg_impl(w, f, k, f.split != 0, kUseSolo);
   // (the sub-strip kernel takes each strip's halo from its own density)
   if (w.n > kSmallN || f.bfix > 0 || f.split != 0 || t.hx == 0) return t;
-  const TileCfg wider = tile_cfg_impl(w, f, k, f.split != 0, true, kReachXSmall);
+  const TileCfg wider = tile_cfg_impl(w, f, k, f.split != 0, kUseSolo, kReachXSmall);
   if (wider.hx <= t.hx) return t;
   f.reach = kReachSmall;
-  return tile_cfg_impl(w, f, k, f.split != 0, true, kReachXSmall);
+  return tile_cfg_impl(w, f, k, f.split != 0, kUseSolo, kReachXSmall);
 }
 
 template <int KMAX, bool kAlign>
@@ -1121,7 +1129,9 @@ hipError_t dispatch_k(int k, F&& f) {
 
 }  // namespace
 
-TileCfg tile_cfg(const DevWs& w, const FastCfg& f, int k) { return tile_cfg_impl(w, f, k, f.split != 0); }
+TileCfg tile_cfg(const DevWs& w, const FastCfg& f, int k, StripUse use) {
+  return tile_cfg_impl(w, f, k, f.split != 0, use);
+}
 
 // The tiles of the plain-strip systems, then those of the sub-strip systems
 // (each launch only when it has items).
@@ -1181,7 +1191,7 @@ hipError_t launch_knn_fov_strips(const DevWs& w, int block, const float* theta, 
   const double alpha = acos(fmax(-1.0, fmin(1.0, c / 4096.0)));
   const double frac = fmax(alpha / 3.141592653589793, 1.0 / 64.0);
   const int ks = static_cast<int>(ceil(k / frac));
-  const TileCfg tc = tile_cfg_impl(w, f, ks, true, true);
+  const TileCfg tc = tile_cfg_impl(w, f, ks, true, kUseSolo);
   f.reach = static_cast<float>(f.reach * sqrt(static_cast<double>(ks) / k));
   AlignArgs a{};
   a.theta = theta;

@@ -228,6 +228,7 @@ bool start_job(nm_server* s, Job* j) {
   sp.sys_id = j->p.sys_id;
   sp.step = 0;
   sp.parity = 0;
+  sp.use = nm::kUseServed;
   const size_t nb = 4 * static_cast<size_t>(j->n);
   if (hipMemcpyAsync(sp.x[0], j->hx.data(), nb, hipMemcpyHostToDevice, s->cs) != hipSuccess ||
       hipMemcpyAsync(sp.y[0], j->hy.data(), nb, hipMemcpyHostToDevice, s->cs) != hipSuccess ||
