@@ -16,8 +16,8 @@
 // the lanes of a wavefront stay together, where clipping a cell candidate by
 // candidate is a serial chain of exact predicates with its own path per lane.
 //
-// Exactness.  c.(c - a) and a x c are exact integers; t is their fp32
-// quotient, within 2^-21 of itself.  Where the two smallest quotients lie
+// Exactness.  c.(c - a) and a x c are exact integers (16-bit offsets) or
+// within 2^-23 of them; t is their fp32 quotient, within 2^-20.4 of itself.  Where the two smallest quotients lie
 // within 2^-19 of each other the step is decided again in exact integers
 // (cross-multiplied); equal values are co-circular particles, of which the
 // last counter-clockwise is the neighbour (the others' cells only touch).
@@ -31,7 +31,11 @@
 //
 // Bound by VALU issue: about 17 instructions per candidate and step, 56
 // candidates and 6 steps per particle at the mean (the longest row of a
-// wavefront, 9 to 10, sets its steps).  Rows of 2^20 uniform particles: 1.95
+// wavefront, 9 to 10, sets its steps): 12,550 instructions a wave, issued 84%
+// of the time, 54% of the lanes active.  Offsets of more than 16 bits (sparse
+// systems) take fp32 sums of products with their rounding put back (60,000
+// particles, 256 queries a strip: 106 us, 115 with fp64 products and their
+// conversions).  Rows of 2^20 uniform particles: 1.95
 // ms by clipping alone, 0.53 ms so (0.49 the strips, 0.02 the rows they
 // leave); of 250,000: 633 us, now 172 + 29.
 #include "strip.h"
@@ -182,7 +186,7 @@ __device__ __forceinline__ int vor_star(const int* lpos, int b, int e, int self,
     float t0 = INFINITY, t1 = INFINITY;  // the two smallest t
     int next = -1;
     const int perp = pack_rel(-ay, ax);  // (narrow) a x c = c . perp
-    const double axd = ax, ayd = ay;
+    const float axf = static_cast<float>(ax), ayf = static_cast<float>(ay);
     auto round = [&](int i, bool tail) {
       float t[kUnroll];
       if (kWide) {
@@ -191,11 +195,16 @@ __device__ __forceinline__ int vor_star(const int* lpos, int b, int e, int self,
         for (int u = 0; u < kUnroll; ++u) c[u] = lpos2[i + u];
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
-          // products below 2^41, exact in fp64
-          const double cx = c[u].x - pq, cy = c[u].y - pqy;
-          const double num = cx * (cx - axd) + cy * (cy - ayd), den = axd * cy - ayd * cx;
-          const float q = static_cast<float>(num) * __builtin_amdgcn_rcpf(static_cast<float>(den));
-          t[u] = den > 0.0 ? q : INFINITY;
+          // fp32 offsets are exact (below 2^24); a sum or difference of two
+          // products with the rounding of one put back is within 2^-23 of
+          // itself, and zero only where it is zero
+          const float cx = static_cast<float>(c[u].x - pq), cy = static_cast<float>(c[u].y - pqy);
+          const float ex = cx - axf, ey = cy - ayf;
+          const float p = cy * ey, q = ayf * cx;
+          const float num = fmaf(cx, ex, p) + fmaf(cy, ey, -p);
+          const float den = fmaf(axf, cy, -q) - fmaf(ayf, cx, -q);
+          const float v = num * __builtin_amdgcn_rcpf(den);
+          t[u] = den > 0.0f ? v : INFINITY;
         }
       } else {
         int c[kUnroll];
@@ -275,7 +284,7 @@ __device__ __host__ __forceinline__ int vor_half(float rho) {
 
 // kStale: only the rows marked in `stale` (by particle), else every row.
 // Nothing runs when `gate` is given and *gate is 0.
-template <bool kStale>
+template <bool kStale, bool kWide>
 __global__ __launch_bounds__(kBlock) void k_vor_strip(DevWs w, TileCfg tc, int dmax, int32_t* __restrict__ ring,
                                                       int32_t* __restrict__ deg,
                                                       const uint8_t* __restrict__ stale,
@@ -309,7 +318,7 @@ __global__ __launch_bounds__(kBlock) void k_vor_strip(DevWs w, TileCfg tc, int d
   const int tyi = tile / tc.ntx, txi = tile - tyi * tc.ntx;
   const int x0 = txi * tc.tw, y0 = tyi * tc.th, ty = min(tc.th, G - y0);
   const int tw = tc.tw, hy = tc.hy;
-  const bool wide = tc.wide != 0;
+  constexpr bool wide = kWide;
   const float domain = static_cast<float>(w.box >> 3);
   const int cap = min(kVsCap, dmax);
   // the halo's width from the strip's own density, never wider than the grid's
@@ -400,8 +409,7 @@ __global__ __launch_bounds__(kBlock) void k_vor_strip(DevWs w, TileCfg tc, int d
             const int b = s_rbase[cy - half], e = s_rbase[cy + half + 1];
             int first = 0;
             uint16_t* col = s_col + threadIdx.x;
-            const int m = wide ? vor_star<true>(lpos, b, e, self, gl, gr, gd, gu, cap, domain, col, first)
-                               : vor_star<false>(lpos, b, e, self, gl, gr, gd, gu, cap, domain, col, first);
+            const int m = vor_star<kWide>(lpos, b, e, self, gl, gr, gd, gu, cap, domain, col, first);
             if (m > 0) {
               const int who = lidx[self];
               int32_t* row = ring + static_cast<int64_t>(who) * dmax;
@@ -535,6 +543,8 @@ __global__ __launch_bounds__(64 * kVwWaves) void k_vor_wave(DevWs w, int dmax, i
   const int nl = static_cast<int>(min<uint32_t>(w.hdr->nvstale, static_cast<uint32_t>(w.n)));
   const int sh = 32 - w.log2_box, cw = 1 << w.log2_w, gm = w.G - 1;
   const float domain = static_cast<float>(w.box >> 3);
+  const float rho = static_cast<float>(w.n) / static_cast<float>(w.C);
+  const int guess = max(1, min(min(15, (w.G - 2) / 2), static_cast<int>(0.5f * (sqrtf(kVwWant / rho) - 1.0f))));
   for (int k = blockIdx.x * kVwWaves + wave; k < nl; k += gridDim.x * kVwWaves) {
     const int s = w.rank[k];
     const int4 q = w.sorted[s];
@@ -542,7 +552,10 @@ __global__ __launch_bounds__(64 * kVwWaves) void k_vor_wave(DevWs w, int dmax, i
     const int ox = q.x & (cw - 1), oy = q.y & (cw - 1);
     bool done = false;
     int had = 0;
-    for (int half = 1; half <= 15 && 2 * half + 2 <= w.G && !done; ++half) {
+    // from the block that should hold enough at the mean density (a block too
+    // dense for it: from the smallest)
+    bool smaller = guess > 1;
+    for (int half = guess; half <= 15 && 2 * half + 2 <= w.G && !done; ++half) {
       // row l / 2 of the block, the part before (0) or after (1) the box edge
       int beg = 0, cnt = 0;
       {
@@ -573,7 +586,13 @@ __global__ __launch_bounds__(64 * kVwWaves) void k_vor_wave(DevWs w, int dmax, i
         if (lane >= o) incl += t;
       }
       const int n = __shfl(incl, 63, 64);
+      if (n > kVwCands && smaller) {
+        smaller = false;
+        half = 0;
+        continue;
+      }
       if (n > kVwCands) break;  // too dense for larger blocks
+      smaller = false;
       // blocks too sparse to hold a star are passed over, unless they are the last
       const bool last = half == 15 || 2 * half + 4 > w.G;
       if (n < kVwWant && !last) continue;
@@ -711,21 +730,25 @@ __global__ __launch_bounds__(64 * kVwWaves) void k_vor_wave(DevWs w, int dmax, i
 }
 
 // Strip geometry: blocks of vor_half cells around the query's cell, about 256
-// queries a strip, halo within the staging buffer; false where a block would
+// queries a strip, or 128 where 256 would leave CUs with one strip or none
+// (60,000 particles: 106 -> 83 us, 120,000: 114 -> 91, 250,000: 173 and 174,
+// 2^20: 476 -> 549), one column where offsets take 32 bits (4096 particles: 78
+// -> 62 us); halo within the staging buffer; false where a block would
 // meet itself around the box (the general kernel takes such grids).
 bool vor_cfg(const DevWs& w, TileCfg& t) {
   const double rho = static_cast<double>(w.n) / static_cast<double>(w.C);
   if (rho < 1e-6) return false;
   const int half = vor_half(static_cast<float>(rho));
   const int hx = max(1, min(half, 15)), hy = max(1, min(half + 1, 15));  // (rows: sparser than the mean)
-  int tw = hx >= 3 ? 2 : 1;
+  int tw = hx >= 3 && (static_cast<long long>(2 + 2 * hx) << w.log2_w) < 32768 ? 2 : 1;
   while (tw < 16 && 2 * tw <= w.G && 256.0 / (tw * rho) > 1.1 * (kTwRows - 2 * hy)) tw *= 2;
   if (half > 15 || tw + 2 * hx > w.G || 2 * hy + 1 > w.G) return false;
   const int W = tw + 2 * hx;
   const bool narrow = (static_cast<long long>(W) << w.log2_w) < 32768 &&
                       (static_cast<long long>(2 * hy + 1) << w.log2_w) < 32768;
   const int room = narrow ? kStripPts : kStripPts / 2;
-  int th = max(1, min(static_cast<int>(ceil(256.0 / (tw * rho))), w.G));
+  const double queries = w.n < 200000 ? 128.0 : 256.0;
+  int th = max(1, min(static_cast<int>(ceil(queries / (tw * rho))), w.G));
   while (th > 1 && (th + 2 * hy > kStripRows || (th + 2 * hy) * W * rho > 0.75 * room)) --th;
   if (th + 2 * hy > kStripRows) return false;
   t = TileCfg{tw, th, hx, hy, w.G / tw, (w.G + th - 1) / th, 2 * hy + 1, narrow ? 0 : 1};
@@ -743,11 +766,15 @@ bool launch_vor_strips(const DevWs& w, int dmax, int32_t* ring, int32_t* deg, co
                        const uint32_t* gate, hipStream_t s) {
   TileCfg tc;
   if (!vor_cfg(w, tc)) return false;
-  const dim3 grid(tc.ntx * tc.nty);
-  if (stale)
-    hipLaunchKernelGGL(k_vor_strip<true>, grid, dim3(kBlock), 0, s, w, tc, dmax, ring, deg, stale, gate);
+  const dim3 grid(tc.ntx * tc.nty), block(kBlock);
+  if (stale && tc.wide)
+    hipLaunchKernelGGL((k_vor_strip<true, true>), grid, block, 0, s, w, tc, dmax, ring, deg, stale, gate);
+  else if (stale)
+    hipLaunchKernelGGL((k_vor_strip<true, false>), grid, block, 0, s, w, tc, dmax, ring, deg, stale, gate);
+  else if (tc.wide)
+    hipLaunchKernelGGL((k_vor_strip<false, true>), grid, block, 0, s, w, tc, dmax, ring, deg, stale, gate);
   else
-    hipLaunchKernelGGL(k_vor_strip<false>, grid, dim3(kBlock), 0, s, w, tc, dmax, ring, deg, stale, gate);
+    hipLaunchKernelGGL((k_vor_strip<false, false>), grid, block, 0, s, w, tc, dmax, ring, deg, stale, gate);
   const int nb = (w.n + kVwWaves - 1) / kVwWaves;
   hipLaunchKernelGGL(k_vor_wave, dim3(min(nb, kVwGridMax)), dim3(64 * kVwWaves), 0, s, w, dmax, ring, deg);
   return true;
