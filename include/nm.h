@@ -266,7 +266,8 @@ int nm_voronoi_check(const nm_grid* g, void* ws, const int32_t* x, const int32_t
  * x, y, whose cells ws must hold (nm_build_cells / nm_bin_step with x, y):
  * twice, nm_voronoi_check, then the stale rows recomputed and the others
  * rotated to start at the +x axis again; then the check once more, and if
- * any row still fails, every row recomputed.  Afterwards (ring, deg) equal
+ * any row still fails, every row recomputed (all of them at once where the
+ * first check fails many).  Afterwards (ring, deg) equal
  * what nm_voronoi gives for x, y.  nfail (device int32 or NULL) receives
  * the first check's count.  stale: device uint8[n] scratch. */
 int nm_voronoi_update(const nm_grid* g, void* ws, const int32_t* x, const int32_t* y, int32_t dmax,

@@ -59,10 +59,12 @@ struct WsHeader {
   uint32_t nvstale;    // Voronoi rows listed for the general kernel (in rank)
   uint32_t nvfail;     // particles whose Voronoi row failed the last reuse test
   uint32_t nvgo;       // rows failed in the update's last reuse test
+  uint32_t nvfull;     // the update rebuilds every row
+  uint32_t nvkeep;     // ... and kept some that it could not
   uint32_t pad0;
   int64_t off_start;   // bytes from here to start and sorted, for calls that get
   int64_t off_sorted;  // the workspace without its grid
-  int32_t pad[44];
+  int32_t pad[42];
 };
 static_assert(sizeof(WsHeader) == 256, "header is one 256-byte block");
 

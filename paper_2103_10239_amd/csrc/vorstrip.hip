@@ -282,7 +282,8 @@ __device__ __host__ __forceinline__ int vor_half(float rho) {
   return static_cast<int>(ceilf(static_cast<float>(kVsReach) / sqrtf(rho)));
 }
 
-// kStale: only the rows marked in `stale` (by particle), else every row.
+// kStale: only the rows marked in `stale` (by particle) unless the header's
+// nvfull asks for all, else every row.
 // Nothing runs when `gate` is given and *gate is 0.
 template <bool kStale, bool kWide>
 __global__ __launch_bounds__(kBlock) void k_vor_strip(DevWs w, TileCfg tc, int dmax, int32_t* __restrict__ ring,
@@ -300,7 +301,6 @@ __global__ __launch_bounds__(kBlock) void k_vor_strip(DevWs w, TileCfg tc, int d
   __shared__ int s_wsum[kBlock / 64];
   __shared__ uint8_t s_rowid[kStripPts];
   __shared__ uint16_t s_qmap[kStripPts];
-  __shared__ uint16_t s_qsel[kStale ? kStripPts : 1];  // the queries to run
   __shared__ int s_nsel;
   __shared__ uint16_t s_col[kVsCap * kBlock];
   __shared__ int s_sub[kStripRows + 1];  // sub-strips: first row, bit 30 when it cannot be staged
@@ -313,6 +313,7 @@ __global__ __launch_bounds__(kBlock) void k_vor_strip(DevWs w, TileCfg tc, int d
     return;
   }
   if (gate && *gate == 0u) return;
+  const bool all = !kStale || hd->nvfull != 0u;
   const int total = min(w.start[w.C], w.n);
   const int G = w.G, lw = w.log2_w;
   const int tyi = tile / tc.ntx, txi = tile - tyi * tc.ntx;
@@ -366,7 +367,9 @@ __global__ __launch_bounds__(kBlock) void k_vor_strip(DevWs w, TileCfg tc, int d
       next = 0;
     } else {
       int run = nq;
-      if (kStale && staged) {
+      if (kStale && staged && !all) {
+        // the stale queries to the front of the query map: a round's entries
+        // are read before any is written, and go to places read before
         if (threadIdx.x == 0) s_nsel = 0;
         __syncthreads();
         for (int q0 = 0; q0 < nq; q0 += kBlock) {
@@ -378,7 +381,8 @@ __global__ __launch_bounds__(kBlock) void k_vor_strip(DevWs w, TileCfg tc, int d
           int base = 0;
           if (lane == 0 && bal != 0ull) base = atomicAdd(&s_nsel, __popcll(bal));
           base = __shfl(base, 0, 64);
-          if (go) s_qsel[base + __popcll(bal & ((1ull << lane) - 1ull))] = static_cast<uint16_t>(self);
+          __syncthreads();
+          if (go) s_qmap[base + __popcll(bal & ((1ull << lane) - 1ull))] = static_cast<uint16_t>(self);
         }
         __syncthreads();
         run = __builtin_amdgcn_readfirstlane(s_nsel);
@@ -389,7 +393,7 @@ __global__ __launch_bounds__(kBlock) void k_vor_strip(DevWs w, TileCfg tc, int d
         int s = 0;
         if (qi < run) {
           if (staged) {
-            const int self = kStale ? s_qsel[qi] : s_qmap[qi];
+            const int self = s_qmap[qi];
             const int cy = s_rowid[self];
             int rx, oy;
             if (wide) {
@@ -442,7 +446,7 @@ __global__ __launch_bounds__(kBlock) void k_vor_strip(DevWs w, TileCfg tc, int d
             for (int step = kRowStep; step > 0; step >>= 1)
               if (r + step < geo.ty && s_qoff[r + step] <= qi) r += step;
             s = w.start[static_cast<int64_t>(geo.y0 + r) * G + x0] + (qi - s_qoff[r]);
-            defer = !kStale || stale[w.sorted[s].z] != 0;
+            defer = !kStale || all || stale[w.sorted[s].z] != 0;
           }
         }
         vor_list(w, defer, s);

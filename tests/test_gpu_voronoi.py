@@ -289,6 +289,83 @@ def test_update_short_long_and_shared_rows(kind, dmax, move):
     assert _rows_of(R.cpu().numpy(), D.cpu().numpy()) == _oracle_rows(x1, y1, box)
 
 
+# Rounds of stale rows (few failures) and all rows at once (more than one in
+# 512), on strips and on a grid too coarse for them.
+@pytest.mark.parametrize("moved", [1, 3, 4, 5, 40, 4096])
+@pytest.mark.parametrize("w", [1024, 1 << 14])
+def test_update_rebuilds_stale_rows_or_all(moved, w):
+    n, box = 4096, 1 << 16
+    x, y, _ = workloads.uniform(n, box=box, seed_pos=91)
+    ring, deg, st, ws = _gpu_rows(x, y, box, w)
+    assert st == 0
+    rng = np.random.default_rng(moved)
+    x1, y1 = x.copy(), y.copy()
+    who = rng.choice(n, moved, replace=False)
+    x1[who] = (x1[who] + rng.integers(300, 900, moved)) % box
+    R, D, X1, Y1 = _dev(ring, torch.int32), _dev(deg, torch.int32), _dev(x1, torch.int32), _dev(y1, torch.int32)
+    nm.build_cells(ws, X1, Y1)
+    want = _oracle_rows(x1, y1, box)
+    for _ in range(2):  # the second update finds nothing to do
+        nfail = nm.voronoi_update(ws, X1, Y1, R, D)
+        assert nm.check(ws) == 0
+        assert _rows_of(R.cpu().numpy(), D.cpu().numpy()) == want
+    assert int(nfail.item()) == 0
+
+
+def test_update_all_rows_keeps_a_passing_row_beyond_the_domain():
+    # A void whose rim particles' cells reach past L/8: such rows are outside the
+    # lists' domain for nm_voronoi, but rows that pass the reuse test are kept by
+    # the update, also where so many others fail that every row is built again.
+    # (rows by the oracle's definition on the periodic images: scipy's Qhull)
+    from scipy.spatial import Delaunay
+    box, w = 1 << 14, 1 << 10
+    rng = np.random.default_rng(12)
+    x, y, _ = workloads.uniform(3000, box=box, seed_pos=92)
+    far = (x.astype(np.int64) - box // 2) ** 2 + (y.astype(np.int64) - box // 2) ** 2 > (box / 7.6) ** 2
+    x, y = x[far], y[far]
+    n = len(x)
+
+    def rows(px, py):
+        off = np.array([(a, b) for a in (0, -1, 1) for b in (0, -1, 1)]) * box
+        pts = np.concatenate([np.stack([px, py], 1) + o for o in off])
+        t = Delaunay(pts)
+        start, nb = t.vertex_neighbor_vertices
+        out = []
+        for i in range(n):
+            j = nb[start[i]:start[i + 1]]
+            d = pts[j] - pts[i]
+            a = np.arctan2(d[:, 1], d[:, 0]) % (2 * np.pi)
+            out.append((j[np.argsort(a)] % n).astype(np.int32))
+        return out
+
+    near_rim = (x.astype(np.int64) - box // 2) ** 2 + (y.astype(np.int64) - box // 2) ** 2 < (box // 4) ** 2
+    was = rows(x.astype(np.int64), y.astype(np.int64))
+    dmax = max(len(r) for r in was) + 4
+    ring = np.full((n, dmax), -1, np.int32)
+    for i, r in enumerate(was):
+        ring[i, :len(r)] = r
+    deg = np.array([len(r) for r in was], np.int32)
+    # particles away from the void move; those around it stay
+    x1, y1 = x.copy(), y.copy()
+    mv = np.flatnonzero(~near_rim)
+    mv = mv[(np.abs(x[mv] - box // 2) > box // 3) | (np.abs(y[mv] - box // 2) > box // 3)]
+    x1[mv] = (x1[mv] + rng.integers(-60, 61, len(mv))) % box
+    y1[mv] = (y1[mv] + rng.integers(-60, 61, len(mv))) % box
+    ws = nm.Workspace(n, box, w)
+    X1, Y1 = _dev(x1, torch.int32), _dev(y1, torch.int32)
+    nm.build_cells(ws, X1, Y1)
+    nm.voronoi(ws, dmax)
+    assert nm.check(ws) == nm.NM_E_RANGE  # the domain, for every row built anew
+    ws = nm.Workspace(n, box, w)
+    nm.build_cells(ws, X1, Y1)
+    R, D = _dev(ring, torch.int32), _dev(deg, torch.int32)
+    nfail = int(nm.voronoi_update(ws, X1, Y1, R, D).item())
+    assert nm.check(ws) == 0
+    assert nfail * 512 > n
+    got = _rows_of(R.cpu().numpy(), D.cpu().numpy())
+    assert got == [r.tolist() for r in rows(x1.astype(np.int64), y1.astype(np.int64))]
+
+
 def test_update_from_unrelated_rows():
     n, box, w = 4097, 1 << 16, 1024
     xa, ya, _ = workloads.uniform(n, box=box, seed_pos=81)
