@@ -464,101 +464,148 @@ __device__ __forceinline__ void ring_cell(int r, int q, int& dx, int& dy) {
   dy = side == 0 ? -r : (side == 1 ? -r + p : (side == 2 ? r : r - p));
 }
 
-// One deferred query searched by a whole wavefront: for each ring the 64
-// lanes take up to 64 cells at a time, skip cells whose nearest point is
-// farther than the current k-th neighbour, flatten the candidates of the rest
-// across the lanes and evaluate 64 per round; candidates that beat the
-// current k-th are merged one by one (each broadcast to every lane; the list
-// itself is spread over the lanes).  Same stop rule as the lane search.
-// Candidates that fail `filt` are skipped.
-template <int KMAX, class Filter = NoFilter>
-__device__ __forceinline__ bool knn_wave(const DevWs& w, int s, const int4& q, int k, int total,
-                                         int (&slot)[KMAX], const Filter& filt = Filter{}) {
+// LDS of a wavefront's search: where its list's entries change places.
+struct WaveScratch {
+  unsigned long long key[32];
+  int slot[32];
+};
+
+__device__ __forceinline__ unsigned long long read_lane64(unsigned long long v, int l) {
+  const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(v), l);
+  const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(v >> 32), l);
+  return static_cast<unsigned long long>(hi) << 32 | lo;
+}
+
+// One deferred query searched by a whole wavefront.  The 49 cells of rings 0
+// to 3 are looked up at once, one a lane, and searched from the inside: first
+// the rings that hold k others, then the rest; each further ring 64 cells at
+// a time.  Cells whose nearest point is farther than the current k-th
+// neighbour are skipped, and the candidates of the others flattened across
+// the lanes, 64 per round.  Same stop rule as the lane search; candidates
+// that fail `filt` are skipped.  Lane t < k returns the t-th nearest's slot in
+// `mslot`.
+//
+// A search is a chain of memory round trips and of merges.  The list is spread
+// over the wave (lane t holds the t-th nearest so far), and a round's
+// candidates below the current k-th take their places at once: each is
+// broadcast and counted against every lane's entry and candidate, which
+// gives the new ranks, and the entries move through LDS (scratch).
+template <class Filter = NoFilter>
+__device__ __forceinline__ bool knn_wave(const DevWs& w, WaveScratch* scratch, int s, const int4& q, int k,
+                                         int total, int& mslot, const Filter& filt = Filter{}) {
   const int lane = threadIdx.x & 63;
   const int sh = 32 - w.log2_box;
   const int cw = 1 << w.log2_w;
   const int gm = w.G - 1;
   const QueryGeom g(q.x, q.y, w);
-  // The list is spread over the wave: lane t < k holds the t-th nearest so
-  // far (key and slot), so an insertion costs each lane one compare with its
-  // own entry and its left neighbour's instead of a pass over a whole list.
   unsigned long long mine = ~0ull;
-  int mslot = -1;
-  unsigned long long worst = ~0ull;  // the k-th entry, in every lane
-  for (int r = 0; r <= g.rmax; ++r) {
-    const int ncell = r == 0 ? 1 : 8 * r;
-    for (int c0 = 0; c0 < ncell; c0 += 64) {
-      int beg = 0, cnt = 0;
-      if (c0 + lane < ncell) {
-        int dx, dy;
-        ring_cell(r, c0 + lane, dx, dy);
-        if (dx >= g.lo && dx <= g.hi && dy >= g.lo && dy <= g.hi) {
-          const long long gx = axis_gap(dx, g.ox, cw, sh), gy = axis_gap(dy, g.oy, cw, sh);
-          if (gx * gx + gy * gy <= key_bound_d2(worst)) {
-            const int64_t c = static_cast<int64_t>((g.hy + dy) & gm) * w.G + ((g.hx + dx) & gm);
-            beg = w.start[c];
-            cnt = max(min(w.start[c + 1], total) - beg, 0);
-          }
-        }
-      }
-      int incl = cnt;
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const int t = __shfl_up(incl, off, 64);
-        if (lane >= off) incl += t;
-      }
-      const int ntot = __shfl(incl, 63, 64);
-      const int excl = incl - cnt;
-      for (int j0 = 0; j0 < ntot; j0 += 64) {
-        const int j = j0 + lane;
-        int lo = 0;  // owner lane of flattened candidate j: last lane with excl <= j
-#pragma unroll
-        for (int step = 32; step > 0; step >>= 1) {
-          const int probe = lo + step;
-          const int e = __shfl(excl, probe < 64 ? probe : 63, 64);
-          if (probe < 64 && e <= j) lo = probe;
-        }
-        const int ob = __shfl(beg, lo, 64), oe = __shfl(excl, lo, 64);
-        unsigned long long kk = ~0ull;
-        int t = -1;
-        if (j < ntot) {
-          t = ob + (j - oe);
-          if (t != s) {
-            const int4 e = w.sorted[t];
-            const int ex = wrap_axis(e.x - q.x, sh), ey = wrap_axis(e.y - q.y, sh);
-            bool keep = true;
-            if constexpr (Filter::kActive) keep = filt.visible(ex, ey);
-            if (keep) kk = pack_key(static_cast<long long>(ex) * ex + static_cast<long long>(ey) * ey, e.z);
-          }
-        }
-        unsigned long long better = __ballot(kk < worst);
-        while (better) {
-          const int l = __ffsll(static_cast<long long>(better)) - 1;
-          better &= better - 1;
-          const unsigned long long bk = __shfl(kk, l, 64);
-          const int bt = __shfl(t, l, 64);
-          if (bk < worst) {
-            const unsigned long long left = __shfl_up(mine, 1, 64);
-            const int lslot = __shfl_up(mslot, 1, 64);
-            if (lane < k && bk < mine) {
-              const bool shift = lane > 0 && bk < left;  // the new key lands before this entry
-              mine = shift ? left : bk;
-              mslot = shift ? lslot : bt;
-            }
-            worst = __shfl(mine, k - 1, 64);
-          }
-        }
+  mslot = -1;
+  int have = 0;                       // entries of the list
+  unsigned long long worst = ~0ull;  // the k-th entry (uniform)
+  // this lane's cell: slots [beg, beg + cnt) and the squared distance to it
+  int beg = 0, cnt = 0;
+  long long gap2 = 0;
+  auto cell = [&](int r, int p) {
+    int dx, dy;
+    ring_cell(r, p, dx, dy);
+    beg = cnt = 0;
+    if (dx >= g.lo && dx <= g.hi && dy >= g.lo && dy <= g.hi) {
+      const long long gx = axis_gap(dx, g.ox, cw, sh), gy = axis_gap(dy, g.oy, cw, sh);
+      gap2 = gx * gx + gy * gy;
+      if (gap2 <= key_bound_d2(worst)) {
+        const int64_t c = static_cast<int64_t>((g.hy + dy) & gm) * w.G + ((g.hx + dx) & gm);
+        beg = w.start[c];
+        cnt = max(min(w.start[c + 1], total) - beg, 0);
       }
     }
-    if (key_bound_d2(worst) < g.ring_bound(r, cw)) break;
-  }
-  // the list in every lane, in the lane search's layout (nearest first at
-  // KMAX - k)
+  };
+  auto prefix = [&]() {  // candidates of the lanes up to this one
+    int incl = cnt;
 #pragma unroll
-  for (int t = 0; t < KMAX; ++t) {
-    const int src = t - (KMAX - k);
-    const int v = __shfl(mslot, src < 0 ? 0 : src, 64);
-    slot[t] = src < 0 ? -1 : v;
+    for (int off = 1; off < 64; off <<= 1) {
+      const int t = __shfl_up(incl, off, 64);
+      if (lane >= off) incl += t;
+    }
+    return incl;
+  };
+  auto search = [&](int incl, int ntot) {  // the first ntot of the lanes' candidates
+    const int excl = incl - cnt;
+    for (int j0 = 0; j0 < ntot; j0 += 64) {
+      const int j = j0 + lane;
+      int lo = 0;  // owner lane of flattened candidate j: last lane with excl <= j
+#pragma unroll
+      for (int step = 32; step > 0; step >>= 1) {
+        const int probe = lo + step;
+        const int e = __shfl(excl, probe < 64 ? probe : 63, 64);
+        if (probe < 64 && e <= j) lo = probe;
+      }
+      const int ob = __shfl(beg, lo, 64), oe = __shfl(excl, lo, 64);
+      unsigned long long kk = ~0ull;
+      const int t = ob + (j - oe);
+      if (j < ntot && t != s) {
+        const int4 e = w.sorted[t];
+        const int ex = wrap_axis(e.x - q.x, sh), ey = wrap_axis(e.y - q.y, sh);
+        bool keep = true;
+        if constexpr (Filter::kActive) keep = filt.visible(ex, ey);
+        if (keep) kk = pack_key(static_cast<long long>(ex) * ex + static_cast<long long>(ey) * ey, e.z);
+      }
+      const unsigned long long better = __ballot(kk < worst);
+      if (better == 0ull) continue;
+      int rc = 0, rl = lane;  // new ranks of this lane's candidate and entry (keys are distinct)
+      for (unsigned long long m = better; m != 0ull; m &= m - 1) {
+        const int l = __ffsll(static_cast<long long>(m)) - 1;
+        const unsigned long long bk = read_lane64(kk, l);
+        const bool before = bk < mine;
+        rc += bk < kk ? 1 : 0;
+        rl += before ? 1 : 0;
+        const int above = have - __popcll(__ballot(lane < have && before));  // entries before the candidate
+        rc += lane == l ? above : 0;
+      }
+      if (lane < have && rl < k) {
+        scratch->key[rl] = mine;
+        scratch->slot[rl] = mslot;
+      }
+      if (kk < worst && rc < k) {
+        scratch->key[rc] = kk;
+        scratch->slot[rc] = t;
+      }
+      have = min(k, have + static_cast<int>(__popcll(better)));
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      if (lane < have) {
+        mine = scratch->key[lane];
+        mslot = scratch->slot[lane];
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      if (have == k) worst = read_lane64(mine, k - 1);
+    }
+  };
+  {  // rings 0 to 3, whose lanes begin at 0, 1, 9 and 25
+    const int r = lane == 0 ? 0 : (lane < 9 ? 1 : (lane < 25 ? 2 : 3));
+    if (lane < 49) cell(r, lane - (2 * r - 1) * (2 * r - 1) * (r > 0 ? 1 : 0));
+    const int incl = prefix();
+    int inner = 3;  // the rings that hold k others than the query
+    for (int t = 2; t >= 0; --t)
+      if (__builtin_amdgcn_readlane(incl, (2 * t + 1) * (2 * t + 1) - 1) > k) inner = t;
+    search(incl, __builtin_amdgcn_readlane(incl, (2 * inner + 1) * (2 * inner + 1) - 1));
+    if (key_bound_d2(worst) < g.ring_bound(inner, cw)) return true;
+    if (inner < 3) {
+      if (r <= inner || gap2 > key_bound_d2(worst)) cnt = 0;
+      const int rest = prefix();
+      search(rest, __builtin_amdgcn_readlane(rest, 63));
+      if (key_bound_d2(worst) < g.ring_bound(3, cw)) return true;
+    }
+  }
+  for (int r = 4; r <= g.rmax; ++r) {
+    const int ncell = 8 * r;
+    for (int c0 = 0; c0 < ncell; c0 += 64) {
+      beg = cnt = 0;
+      if (c0 + lane < ncell) cell(r, c0 + lane);
+      const int incl = prefix();
+      search(incl, __builtin_amdgcn_readlane(incl, 63));
+    }
+    if (key_bound_d2(worst) < g.ring_bound(r, cw)) break;
   }
   return worst != ~0ull;
 }
@@ -872,21 +919,40 @@ __device__ __forceinline__ void knn_tile_body(const DevWs& w, const FastCfg& f, 
   } else if (kMode != kFieldOfView && nl > 48) {
     for (int j = threadIdx.x; j < nl; j += kBlock) exact_lane<KMAX, kAlign>(w, s_dq[j], k, total, nbr, d2out, a);
   } else {
-    for (int j = threadIdx.x >> 6; j < nl; j += kBlock / 64) {
-      const int sq = s_dq[j];
+    // Lane c of a wavefront keeps the list of its c-th query, and the lanes
+    // finish their queries together.
+    static_assert(kDeferCap <= 64 * (kBlock / 64), "a lane for each of a wavefront's queries");
+    WaveScratch* scratch = reinterpret_cast<WaveScratch*>(lpos_store) + (threadIdx.x >> 6);  // (staging is over)
+    int slot[KMAX];
+#pragma unroll
+    for (int t = 0; t < KMAX; ++t) slot[t] = 0;
+    int mine = -1;
+    bool found = false;
+    int c = 0;
+    for (int j = threadIdx.x >> 6; j < nl; j += kBlock / 64, ++c) {
+      const int sq = __builtin_amdgcn_readfirstlane(s_dq[j]);
       const int4 q = w.sorted[sq];
-      int slot[KMAX];
+      int ms;
       bool ok;
       if constexpr (kMode == kFieldOfView)
-        ok = knn_wave<KMAX>(w, sq, q, k, total, slot, FovFilter{fov_heading(a.theta[q.z], a.cone)});
+        ok = knn_wave(w, scratch, sq, q, k, total, ms, FovFilter{fov_heading(a.theta[q.z], a.cone)});
       else
-        ok = knn_wave<KMAX>(w, sq, q, k, total, slot);
-      if (lane == 0) {
-        if (ok)
-          finish_query<KMAX, kAlign>(w, sq, q, slot, k, nbr, d2out, a);
-        else
-          set_err(w.hdr, NM_E_RANGE);  // fewer than k other (visible) particles were binned
+        ok = knn_wave(w, scratch, sq, q, k, total, ms);
+#pragma unroll
+      for (int t = 0; t < KMAX; ++t) {
+        const int v = __builtin_amdgcn_readlane(ms, max(t - (KMAX - k), 0));
+        if (lane == c) slot[t] = v;
       }
+      if (lane == c) {
+        mine = sq;
+        found = ok;
+      }
+    }
+    if (mine >= 0) {
+      if (found)
+        finish_query<KMAX, kAlign>(w, mine, w.sorted[mine], slot, k, nbr, d2out, a);
+      else
+        set_err(w.hdr, NM_E_RANGE);  // fewer than k other (visible) particles were binned
     }
   }
   if (nd > kDeferCap) {

@@ -533,6 +533,35 @@ def test_knn_wide_strips_near_ties(k, block):
     assert np.array_equal(nbr, rn) and np.array_equal(d2, rd)
 
 
+# Searches by a wavefront (no staged strips, few queries a strip): lists that
+# rings 0 to 3 hold and that they don't, grids the rings wrap around, rounds of
+# more candidates than the list, equal distances, exactly k others.
+@pytest.mark.parametrize("k", [1, 2, 7, 20, 31, 32])
+@pytest.mark.parametrize("points,w", [("few", 1 << 12), ("sparse", 1 << 10), ("sparse", 1 << 13), ("clumps", 1 << 10),
+                                      ("clumps", 1 << 11), ("lattice", 1 << 12)])
+def test_knn_wave_searches(points, w, k):
+    box = 1 << 16
+    rng = np.random.default_rng(k)
+    if points == "few":
+        x, y = rng.integers(0, box, (2, k + 1))
+    elif points == "sparse":
+        x, y = rng.integers(0, box, (2, 150))
+    elif points == "clumps":  # far apart, each a few cells wide, none with more than k others
+        c = rng.integers(0, box, (2, 9))
+        x, y = (np.repeat(c, max(k // 2, 2), axis=1) + rng.integers(0, 3000, (2, 9 * max(k // 2, 2)))) % box
+    else:
+        x, y = (np.stack(np.meshgrid(np.arange(16), np.arange(16))).reshape(2, -1) * (box // 16)).astype(np.int64)
+    if len(x) <= k:
+        pytest.skip("fewer than k others")
+    x, y = x.astype(np.int32), y.astype(np.int32)
+    ws = nm.Workspace(len(x), box, w, block=-1)
+    nm.build_cells(ws, _dev(x, torch.int32), _dev(y, torch.int32))
+    nbr, d2 = nm.knn(ws, k, with_d2=True)
+    assert nm.check(ws) == 0
+    rn, rd = oracle.knn(x, y, box, k)
+    assert np.array_equal(nbr.cpu().numpy(), rn) and np.array_equal(d2.cpu().numpy(), rd)
+
+
 @pytest.mark.parametrize("block", [-1, 0, 3, 4, 5, 6, 8, nm.NM_BLOCK_SUBSTRIPS, nm.NM_BLOCK_SUBSTRIPS | 5])
 @pytest.mark.parametrize("kind,n,k,w", [("uniform", 20013, 7, 4096), ("uniform", 20013, 1, 8192),
                                         ("uniform", 20013, 20, 4096), ("clustered", 20013, 12, 2048),
