@@ -992,7 +992,7 @@ template <int KMAX, bool kAlign, int kMode>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kKnnWaves<KMAX>))) void k_knn(DevWs w, FastCfg f, TileCfg tc, int k,
                                                 int32_t* __restrict__ nbr,
                                                 long long* __restrict__ d2out, AlignArgs a) {
-  knn_tile_body<KMAX, kAlign, kMode>(w, f, tc, k, nbr, d2out, a, xcd_tile(blockIdx.x, gridDim.x));
+  knn_tile_body<KMAX, kAlign, kMode>(w, f, tc, k, nbr, d2out, a, xcd_run(blockIdx.x, gridDim.x));
 }
 
 // Field-of-view lists over the same strips (a.theta: headings, a.cone: the
@@ -1000,7 +1000,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kKnnWave
 template <int KMAX>
 __global__ __launch_bounds__(kBlock) void k_knn_fov_strip(DevWs w, FastCfg f, TileCfg tc, int k,
                                                           int32_t* __restrict__ nbr, AlignArgs a) {
-  knn_tile_body<KMAX, false, kFieldOfView>(w, f, tc, k, nbr, nullptr, a, xcd_tile(blockIdx.x, gridDim.x));
+  knn_tile_body<KMAX, false, kFieldOfView>(w, f, tc, k, nbr, nullptr, a, xcd_run(blockIdx.x, gridDim.x));
 }
 
 template <int KMAX>

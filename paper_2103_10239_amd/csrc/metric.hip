@@ -491,7 +491,7 @@ __global__ __launch_bounds__(kBlock) void k_metric_count(DevWs w, MetricCfg mc, 
     if (blockIdx.x == 0 && threadIdx.x == 0) set_err(w.hdr, NM_E_INVAL);
     return;
   }
-  strip_tile(w, mc, xcd_tile(blockIdx.x, gridDim.x), CountOp{offsets, static_cast<unsigned long long>(rc2)});
+  strip_tile(w, mc, xcd_run(blockIdx.x, gridDim.x), CountOp{offsets, static_cast<unsigned long long>(rc2)});
 }
 
 __global__ __launch_bounds__(kBlock) void k_metric_count_rest(DevWs w, MetricCfg mc, long long rc2,
@@ -872,7 +872,7 @@ __global__ __launch_bounds__(kBlock) void k_metric_fill(DevWs w, MetricCfg mc, l
     if (blockIdx.x == 0 && threadIdx.x == 0) set_err(w.hdr, NM_E_CAPACITY);
     return;
   }
-  strip_tile(w, mc, xcd_tile(blockIdx.x, gridDim.x), FillOp{offsets, idx, rc2, nnz, key_shift(rc2)});
+  strip_tile(w, mc, xcd_run(blockIdx.x, gridDim.x), FillOp{offsets, idx, rc2, nnz, key_shift(rc2)});
 }
 
 // The listed chunks, then one wave per deferred row: its keys gathered into

@@ -307,7 +307,7 @@ __global__ __launch_bounds__(kBlock) void k_vor_strip(DevWs w, TileCfg tc, int d
   __shared__ int s_nsub;
   int* lpos = reinterpret_cast<int*>(lpos_store);
   const WsHeader* hd = w.hdr;
-  const int tile = xcd_tile(blockIdx.x, gridDim.x);
+  const int tile = xcd_run(blockIdx.x, gridDim.x);
   if (hd->built != kBuilt || hd->n != w.n || hd->box != w.box || hd->cell_w != w.cell_w) {
     if (tile == 0 && threadIdx.x == 0) set_err(w.hdr, NM_E_INVAL);
     return;
