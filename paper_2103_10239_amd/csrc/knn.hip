@@ -649,15 +649,15 @@ enum StripMode {
                         // queries and the uncertified ones take the exact search
 };
 
-template <int KMAX, bool kAlign, int kMode>
+template <int KMAX, bool kAlign, int kMode, int kPts>
 __device__ __forceinline__ void knn_tile_body(const DevWs& w, const FastCfg& f, const TileCfg& tc,
                                               int k, int32_t* __restrict__ nbr,
                                               long long* __restrict__ d2out, const AlignArgs& a,
                                               int tile) {
   // packed 16-bit pairs, or int32 pairs (wide); padded so that a round of
   // kUnroll reads past a block's last candidate stays inside the buffer
-  __shared__ int2 lpos_store[kStripPts / 2 + kUnroll];
-  __shared__ int lidx[kStripPts];          // particle index of each staged particle
+  __shared__ int2 lpos_store[kPts / 2 + kUnroll];
+  __shared__ int lidx[kPts];               // particle index of each staged particle
   __shared__ int s_rbase[kStripRows + 1];  // LDS offset of each halo row
   __shared__ int s_ga0[kStripRows];        // first slot of the row's first piece
   __shared__ int s_n0[kStripRows];         // particles in the row's first piece
@@ -667,8 +667,8 @@ __device__ __forceinline__ void knn_tile_body(const DevWs& w, const FastCfg& f, 
   __shared__ int s_wsum[kBlock / 64];
   __shared__ int s_defer;
   __shared__ int s_dq[kDeferCap];  // slots of the strip's uncertified queries
-  __shared__ uint8_t s_rowid[kStripPts];   // halo row of each staged particle
-  __shared__ uint16_t s_qmap[kStripPts];   // LDS index of each of the strip's queries
+  __shared__ uint8_t s_rowid[kPts];        // halo row of each staged particle
+  __shared__ uint16_t s_qmap[kPts];        // LDS index of each of the strip's queries
   __shared__ int s_sub[kStripRows + 1];    // sub-strip rows (kOverflowSplit)
   __shared__ int s_nsub;
   int* lpos = reinterpret_cast<int*>(lpos_store);
@@ -834,7 +834,7 @@ __device__ __forceinline__ void knn_tile_body(const DevWs& w, const FastCfg& f, 
     // Staging is a chain of global reads and barriers: its waves issue first
     // (wave priority), so that other strips' searches fill the gaps.
     __builtin_amdgcn_s_setprio(3);
-    const bool staged = strip_stage<true>(w, geo, strip_lds(), total, npts, nq);
+    const bool staged = strip_stage<true, kPts>(w, geo, strip_lds(), total, npts, nq);
     __builtin_amdgcn_s_setprio(0);
     if (nq == 0) return;
     for (int qi = threadIdx.x; qi < nq; qi += kBlock) {
@@ -854,7 +854,7 @@ __device__ __forceinline__ void knn_tile_body(const DevWs& w, const FastCfg& f, 
     for (;;) {
       int np_cur, nq_cur;
       __builtin_amdgcn_s_setprio(3);
-      const bool st = strip_stage<true>(w, geo, strip_lds(), total, np_cur, nq_cur);
+      const bool st = strip_stage<true, kPts>(w, geo, strip_lds(), total, np_cur, nq_cur);
       __builtin_amdgcn_s_setprio(0);
       nq_cur = __builtin_amdgcn_readfirstlane(nq_cur);  // block-uniform: keep it scalar
       bool plan = false;
@@ -863,7 +863,7 @@ __device__ __forceinline__ void knn_tile_body(const DevWs& w, const FastCfg& f, 
         plan = !st && hx > 0;
       }
       if (plan) {
-        const int cap = wide ? kStripPts / 2 : kStripPts;
+        const int cap = wide ? kPts / 2 : kPts;
         if (threadIdx.x == 0) {
           int ns = 0;
           for (int r0 = 0; r0 < tb.ty;) {
@@ -988,11 +988,21 @@ constexpr int kKnnWaves = (KMAX >= 12 && KMAX <= 20) ? 4 : (KMAX <= 8 ? 5 : 3);
 template <int KMAX>
 constexpr int kBatchKnnWaves = KMAX <= 8 ? 4 : kKnnWaves<KMAX>;
 
+// Particles a strip stages: what the LDS of a CU holds for that many strips
+// (kStripPts for all: 2^22 clustered particles, k = 20 2035 -> 2016 us; 200,003
+// clustered, k = 31 484 -> 471; 512 batched systems of 256 to 65,536, k = 7
+// 1.60-1.74 -> 1.54 ms; 16 served jobs 4.5 -> 4.3 ms).
+constexpr int strip_pts(int waves) { return waves >= 5 ? kStripPts : (waves == 4 ? 3328 : 4480); }
+template <int KMAX>
+constexpr int kKnnPts = strip_pts(kKnnWaves<KMAX>);
+template <int KMAX>
+constexpr int kBatchKnnPts = strip_pts(kBatchKnnWaves<KMAX>);
+
 template <int KMAX, bool kAlign, int kMode>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kKnnWaves<KMAX>))) void k_knn(DevWs w, FastCfg f, TileCfg tc, int k,
                                                 int32_t* __restrict__ nbr,
                                                 long long* __restrict__ d2out, AlignArgs a) {
-  knn_tile_body<KMAX, kAlign, kMode>(w, f, tc, k, nbr, d2out, a, xcd_run(blockIdx.x, gridDim.x));
+  knn_tile_body<KMAX, kAlign, kMode, kKnnPts<KMAX>>(w, f, tc, k, nbr, d2out, a, xcd_run(blockIdx.x, gridDim.x));
 }
 
 // Field-of-view lists over the same strips (a.theta: headings, a.cone: the
@@ -1000,7 +1010,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kKnnWave
 template <int KMAX>
 __global__ __launch_bounds__(kBlock) void k_knn_fov_strip(DevWs w, FastCfg f, TileCfg tc, int k,
                                                           int32_t* __restrict__ nbr, AlignArgs a) {
-  knn_tile_body<KMAX, false, kFieldOfView>(w, f, tc, k, nbr, nullptr, a, xcd_run(blockIdx.x, gridDim.x));
+  knn_tile_body<KMAX, false, kFieldOfView, kStripPts>(w, f, tc, k, nbr, nullptr, a, xcd_run(blockIdx.x, gridDim.x));
 }
 
 template <int KMAX>
@@ -1057,7 +1067,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kBatchKn
     const TileCfg tc = uniform_load(&g->tc);
     const AlignArgs a = uniform_load_align(g);
     const int li = it - __builtin_amdgcn_readfirstlane(g->base[kSt]);
-    knn_tile_body<KMAX, true, kMode>(w, f, tc, k, uniform_ptr(g->nbr), nullptr, a, li);
+    knn_tile_body<KMAX, true, kMode, kBatchKnnPts<KMAX>>(w, f, tc, k, uniform_ptr(g->nbr), nullptr, a, li);
     __syncthreads();
   }
 }
@@ -1076,8 +1086,8 @@ inline double solo_strip_queries(int n) {
 // half width.  The strip height aims at about 256 queries; the halo must fit
 // the staging buffer and the row table, W <= G (a block never meets itself
 // around the box), and narrow strips keep every block under 2^15 units.
-// `reach_x`: half width in mean k-th-neighbour radii.
-TileCfg tile_cfg_impl(const DevWs& w, const FastCfg& f, int k, bool narrow_strips, StripUse use = kUseBatch,
+// `reach_x`: half width in mean k-th-neighbour radii; `pts`: particles staged.
+TileCfg tile_cfg_impl(const DevWs& w, const FastCfg& f, int k, bool narrow_strips, int pts, StripUse use = kUseBatch,
                       double reach_x = kReachX) {
   const double queries = use == kUseSolo ? solo_strip_queries(w.n) : kStripQ;
   TileCfg t{1, 1, 0, 0, w.G, w.G, 0, 0};
@@ -1135,7 +1145,7 @@ TileCfg tile_cfg_impl(const DevWs& w, const FastCfg& f, int k, bool narrow_strip
   const int W = tw + 2 * hx;
   const bool narrow = (static_cast<long long>(W) << w.log2_w) < 32768 &&
                       (static_cast<long long>(2 * hy + 1) << w.log2_w) < 32768;
-  const int cap = narrow ? kStripPts : kStripPts / 2;
+  const int cap = narrow ? pts : pts / 2;
   int th = static_cast<int>(ceil(queries / (tw * rr)));
   th = max(1, min(th, w.G));
   const double fill = use == kUseServed && !narrow ? kFillServed : 0.75;
@@ -1150,31 +1160,6 @@ TileCfg tile_cfg_impl(const DevWs& w, const FastCfg& f, int k, bool narrow_strip
   t.bmax = min(2 * hy + 1, w.G);
   t.wide = narrow ? 0 : 1;
   return t;
-}
-
-// The strips of a system run by itself (f.reach too may grow for small ones).
-TileCfg solo_cfg(const DevWs& w, FastCfg& f, int k) {
-  const TileCfg t = tile_cfg_impl(w, f, k, f.split != 0, kUseSolo);
-  // (the sub-strip kernel takes each strip's halo from its own density)
-  if (w.n > kSmallN || f.bfix > 0 || f.split != 0 || t.hx == 0) return t;
-  const TileCfg wider = tile_cfg_impl(w, f, k, f.split != 0, kUseSolo, kReachXSmall);
-  if (wider.hx <= t.hx) return t;
-  f.reach = kReachSmall;
-  return tile_cfg_impl(w, f, k, f.split != 0, kUseSolo, kReachXSmall);
-}
-
-template <int KMAX, bool kAlign>
-hipError_t launch_t(const DevWs& w, FastCfg f, int k, int32_t* nbr, long long* d2,
-                    const AlignArgs& a, hipStream_t s) {
-  const TileCfg tc = solo_cfg(w, f, k);
-  const int ntiles = tc.ntx * tc.nty;
-  if (f.split && tc.hx > 0)
-    hipLaunchKernelGGL((k_knn<KMAX, kAlign, kOverflowSplit>), dim3(ntiles), dim3(kBlock), 0, s, w, f,
-                       tc, k, nbr, d2, a);
-  else
-    hipLaunchKernelGGL((k_knn<KMAX, kAlign, kOverflowGlobal>), dim3(ntiles), dim3(kBlock), 0, s, w, f,
-                       tc, k, nbr, d2, a);
-  return hipGetLastError();
 }
 
 // Register list sizes compiled; a request for k uses the smallest KMAX >= k.
@@ -1193,10 +1178,49 @@ hipError_t dispatch_k(int k, F&& f) {
   return f(std::integral_constant<int, 32>{});
 }
 
+int solo_pts(int k) {
+  int pts = kStripPts;
+  (void)dispatch_k(k, [&](auto km) {
+    pts = kKnnPts<decltype(km)::value>;
+    return hipSuccess;
+  });
+  return pts;
+}
+
+// The strips of a system run by itself (f.reach too may grow for small ones).
+TileCfg solo_cfg(const DevWs& w, FastCfg& f, int k) {
+  const TileCfg t = tile_cfg_impl(w, f, k, f.split != 0, solo_pts(k), kUseSolo);
+  // (the sub-strip kernel takes each strip's halo from its own density)
+  if (w.n > kSmallN || f.bfix > 0 || f.split != 0 || t.hx == 0) return t;
+  const TileCfg wider = tile_cfg_impl(w, f, k, f.split != 0, solo_pts(k), kUseSolo, kReachXSmall);
+  if (wider.hx <= t.hx) return t;
+  f.reach = kReachSmall;
+  return tile_cfg_impl(w, f, k, f.split != 0, solo_pts(k), kUseSolo, kReachXSmall);
+}
+
+template <int KMAX, bool kAlign>
+hipError_t launch_t(const DevWs& w, FastCfg f, int k, int32_t* nbr, long long* d2,
+                    const AlignArgs& a, hipStream_t s) {
+  const TileCfg tc = solo_cfg(w, f, k);
+  const int ntiles = tc.ntx * tc.nty;
+  if (f.split && tc.hx > 0)
+    hipLaunchKernelGGL((k_knn<KMAX, kAlign, kOverflowSplit>), dim3(ntiles), dim3(kBlock), 0, s, w, f,
+                       tc, k, nbr, d2, a);
+  else
+    hipLaunchKernelGGL((k_knn<KMAX, kAlign, kOverflowGlobal>), dim3(ntiles), dim3(kBlock), 0, s, w, f,
+                       tc, k, nbr, d2, a);
+  return hipGetLastError();
+}
+
 }  // namespace
 
 TileCfg tile_cfg(const DevWs& w, const FastCfg& f, int k, StripUse use) {
-  return tile_cfg_impl(w, f, k, f.split != 0, use);
+  int pts = kStripPts;
+  (void)dispatch_k(k, [&](auto km) {
+    pts = kBatchKnnPts<decltype(km)::value>;
+    return hipSuccess;
+  });
+  return tile_cfg_impl(w, f, k, f.split != 0, pts, use);
 }
 
 // The tiles of the plain-strip systems, then those of the sub-strip systems
@@ -1257,7 +1281,7 @@ hipError_t launch_knn_fov_strips(const DevWs& w, int block, const float* theta, 
   const double alpha = acos(fmax(-1.0, fmin(1.0, c / 4096.0)));
   const double frac = fmax(alpha / 3.141592653589793, 1.0 / 64.0);
   const int ks = static_cast<int>(ceil(k / frac));
-  const TileCfg tc = tile_cfg_impl(w, f, ks, true, kUseSolo);
+  const TileCfg tc = tile_cfg_impl(w, f, ks, true, kStripPts, kUseSolo);
   f.reach = static_cast<float>(f.reach * sqrt(static_cast<double>(ks) / k));
   AlignArgs a{};
   a.theta = theta;

@@ -19,7 +19,7 @@
 
 namespace nm {
 
-constexpr int kStripPts = 2560;           // staged particles (wide strips: half)
+constexpr int kStripPts = 2560;           // staged particles (wide strips: half), at least
 constexpr int kStripRows = 128;           // R <= kStripRows (row tables small enough for 5 strips per CU)
 constexpr int kRowStep = kStripRows / 2;  // binary search over <= kStripRows rows
 constexpr int kTwRows = 256;              // strips widen while ~256 queries need more rows than this
@@ -74,8 +74,8 @@ struct StripGeo {
 };
 
 struct StripLds {
-  int2* lpos_store;  // [kStripPts / 2 + kUnroll] (narrow: read as int[])
-  int* lslot;        // [kStripPts]
+  int2* lpos_store;  // [kPts / 2 + kUnroll] (narrow: read as int[])
+  int* lslot;        // [kPts]
   int* rbase;        // [kStripRows + 1]
   int* ga0;          // [kStripRows] first slot of the row's first piece
   int* n0;           // [kStripRows] particles in the row's first piece
@@ -83,8 +83,8 @@ struct StripLds {
   int* qoff;         // [kStripRows + 1]
   int* tself;        // [kStripRows]
   int* wsum;         // [kBlock / 64]
-  uint8_t* rowid;    // [kStripPts] halo row of each staged particle
-  uint16_t* qmap;    // [kStripPts] LDS index of each query of the strip (may be null)
+  uint8_t* rowid;    // [kPts] halo row of each staged particle
+  uint16_t* qmap;    // [kPts] LDS index of each query of the strip (may be null)
 };
 
 // Cell-ordered slot of staged particle i (the inverse of the staging copy).
@@ -99,7 +99,7 @@ __device__ __forceinline__ int strip_slot(const StripLds& s, int i) {
 // particles of strip g.  Every thread of the workgroup must call it; it ends
 // with a barrier.  Returns whether the particles were staged; npts and nq
 // get the halo's and the strip's particle counts.
-template <bool kStoreIndex>
+template <bool kStoreIndex, int kPts = kStripPts>
 __device__ __forceinline__ bool strip_stage(const DevWs& w, const StripGeo& g, const StripLds& s,
                                             int total, int& npts, int& nq) {
   const int G = w.G, L = w.box, gm = G - 1, lw = w.log2_w;
@@ -153,7 +153,7 @@ __device__ __forceinline__ bool strip_stage(const DevWs& w, const StripGeo& g, c
     s.qoff[g.ty] = nq;
   }
   __syncthreads();
-  const bool staged = nq > 0 && hx > 0 && npts <= (g.wide ? kStripPts / 2 : kStripPts);
+  const bool staged = nq > 0 && hx > 0 && npts <= (g.wide ? kPts / 2 : kPts);
   if (staged) {
     // Row of every staged particle (one thread per halo row), then the
     // particles as offsets from the halo corner, one per thread per round.

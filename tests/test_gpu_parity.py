@@ -533,6 +533,25 @@ def test_knn_wide_strips_near_ties(k, block):
     assert np.array_equal(nbr, rn) and np.array_equal(d2, rd)
 
 
+# Strips that just fit the staging buffer (of 2560, 3328 or 4480 particles by
+# the list's length, half of that on wide strips) and that just don't: all
+# particles in one cell.
+@pytest.mark.parametrize("over", [-1, 0, 1])
+@pytest.mark.parametrize("cap", [2560, 3328, 4480])
+@pytest.mark.parametrize("k", [7, 12, 31])
+@pytest.mark.parametrize("w,part,block", [(1 << 10, 1, 0), (1 << 10, 1, nm.NM_BLOCK_SUBSTRIPS), (1 << 15, 2, 0),
+                                          (1 << 15, 2, nm.NM_BLOCK_SUBSTRIPS)])
+def test_knn_staging_capacity(w, part, block, k, cap, over):
+    n, box = cap // part + over, 16 * w
+    x, y = 5 * w + np.random.default_rng(n).integers(0, w, (2, n)).astype(np.int32)
+    ws = nm.Workspace(n, box, w, block=block)
+    nm.build_cells(ws, _dev(x, torch.int32), _dev(y, torch.int32))
+    nbr, d2 = nm.knn(ws, k, with_d2=True)
+    assert nm.check(ws) == 0
+    rn, rd = oracle.knn(x, y, box, k)
+    assert np.array_equal(nbr.cpu().numpy(), rn) and np.array_equal(d2.cpu().numpy(), rd)
+
+
 # Searches by a wavefront (no staged strips, few queries a strip): lists that
 # rings 0 to 3 hold and that they don't, grids the rings wrap around, rounds of
 # more candidates than the list, equal distances, exactly k others.
