@@ -92,6 +92,71 @@ __device__ __forceinline__ void sort_linked(uint32_t link, int (&v)[KMAX], Exact
   }
 }
 
+// Sorted batches for long lists.  An insertion costs an operation per list
+// entry; a batch of kNetBatch costs 114 operations to sort and 106 (22 entries)
+// or 182 (34) to merge, that is 14 and 19 a candidate.  Insertions and batches:
+// lists of 20 on 2^22 clustered particles 2.00 and 1.83 ms, of 31 on 200,003
+// clustered 456-480 and 399 us.  Lists under kNetBatch entries gain nothing.
+constexpr int kNetBatch = 16;
+
+__device__ __forceinline__ void cmp_swap(uint32_t& a, uint32_t& b) {
+  const uint32_t lo = min(a, b);
+  b = max(a, b);
+  a = lo;
+}
+
+// Batcher's odd-even merge of the sorted halves of v[LO .. LO + N), stride R.
+template <int LO, int N, int R, int M>
+__device__ __forceinline__ void oe_merge(uint32_t (&v)[M]) {
+  if constexpr (2 * R < N) {
+    oe_merge<LO, N, 2 * R>(v);
+    oe_merge<LO + R, N, 2 * R>(v);
+#pragma unroll
+    for (int i = LO + R; i + R < LO + N; i += 2 * R) cmp_swap(v[i], v[i + R]);
+  } else {
+    cmp_swap(v[LO], v[LO + R]);
+  }
+}
+
+// Ascending order: groups of four by median-of-three insertion, then merges.
+__device__ __forceinline__ void sort_batch(uint32_t (&v)[kNetBatch]) {
+#pragma unroll
+  for (int g = 0; g < kNetBatch; g += 4) {
+    const uint32_t a = v[g], b = v[g + 1], c = v[g + 2], e = v[g + 3];
+    const uint32_t lo = min(min(a, b), c), mid = umed3(a, b, c), hi = max(max(a, b), c);
+    v[g] = min(lo, e);
+    v[g + 1] = umed3(lo, mid, e);
+    v[g + 2] = umed3(mid, hi, e);
+    v[g + 3] = max(hi, e);
+  }
+  oe_merge<0, 8, 1>(v);
+  oe_merge<8, 8, 1>(v);
+  oe_merge<0, 16, 1>(v);
+}
+
+// The KS smallest of an ascending list (whose first entries may be the
+// sentinel 0) and an ascending batch, ascending: the minimum of the list's
+// last entries and the reversed batch leaves them as a bitonic sequence,
+// sorted as the last KS places of a power of two whose first are zeros.
+template <int KS>
+__device__ __forceinline__ void merge_batch(uint32_t (&kl)[KS], const uint32_t (&v)[kNetBatch]) {
+  static_assert(KS >= kNetBatch, "the batch meets the list's last entries");
+#pragma unroll
+  for (int j = 0; j < kNetBatch; ++j) kl[KS - 1 - j] = min(kl[KS - 1 - j], v[j]);
+  constexpr int P = KS > 32 ? 64 : (KS > 16 ? 32 : 16);
+  constexpr int off = P - KS;
+#pragma unroll
+  for (int st = P / 2; st > 0; st >>= 1) {
+#pragma unroll
+    for (int i = off; i < P; ++i)
+      if ((i & st) == 0 && i + st < P) cmp_swap(kl[i - off], kl[i + st - off]);
+  }
+}
+
+// Candidates per round of a staged block's loop.
+template <int KS>
+constexpr int kRound = KS >= kNetBatch ? kNetBatch : kUnroll;
+
 // Exact squared distance from a staged query (packed position pq, or x and
 // y) to staged particle i: the 16-bit differences are exact inside a block.
 template <bool kWide>
@@ -351,6 +416,7 @@ __device__ __forceinline__ bool strip_search(const DevWs& w, const TileCfg& tc, 
   // out at the end: cheaper than masking every candidate against it.
   constexpr bool kWithSelf = !Filter::kActive;
   constexpr int KS = kWithSelf ? KT + 1 : KT;
+  constexpr int RN = kRound<KS>;
   const int2* lpos2 = reinterpret_cast<const int2*>(lpos);
   if (Bq > tc.bmax) return false;
   for (int attempt = 0; attempt < 2; ++attempt) {
@@ -365,20 +431,20 @@ __device__ __forceinline__ bool strip_search(const DevWs& w, const TileCfg& tc, 
     if (static_cast<long long>(boundf) > b.bound) boundf = nextafterf(boundf, 0.0f);
     const float scale = ldexpf(1.0f, -sh);
     const int a = rbase[b.r0], e = rbase[b.r0 + Bq];
-    // One round: candidates i .. i + kUnroll - 1.  Only the last round of a
+    // One round: candidates i .. i + RN - 1.  Only the last round of a
     // block (tail) can pass its end; it masks what lies beyond.
     auto round = [&](int i, bool tail) {
-      uint32_t kk[kUnroll];
+      uint32_t kk[RN];
       if (kWide) {
         // fp32 squared distances: the offsets are exact (below 2^24), the
         // square and the sum round twice (relative error below 2^-23, an
         // eighth of a distance-field unit), so every field is within one of
         // the exact one; the certificate below widens its margins to match.
-        int2 pc[kUnroll];
+        int2 pc[RN];
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) pc[u] = lpos2[i + u];  // (buffer padded by kUnroll)
+        for (int u = 0; u < RN; ++u) pc[u] = lpos2[i + u];  // (buffer padded by RN)
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
+        for (int u = 0; u < RN; ++u) {
           const int dxi = pc[u].x - pq, dyi = pc[u].y - pqy;
           const float dx = static_cast<float>(dxi), dy = static_cast<float>(dyi);
           const float d2 = fmaf(dy, dy, dx * dx);
@@ -387,12 +453,12 @@ __device__ __forceinline__ bool strip_search(const DevWs& w, const TileCfg& tc, 
             if (!filt.visible(static_cast<long long>(dxi), static_cast<long long>(dyi))) kk[u] = kKey32Inf;
         }
       } else {
-        int pc[kUnroll];
+        int pc[RN];
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) pc[u] = lpos[i + u];  // (buffer padded by kUnroll)
+        for (int u = 0; u < RN; ++u) pc[u] = lpos[i + u];  // (buffer padded by RN)
         const uint32_t clampd = static_cast<uint32_t>(b.bound);
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
+        for (int u = 0; u < RN; ++u) {
           const uint32_t d2 = rel_d2_u(pc[u], pq);
           kk[u] = ((min(d2, clampd) >> sh) << 13) | static_cast<uint32_t>(i + u);
           if constexpr (Filter::kActive) {
@@ -402,16 +468,28 @@ __device__ __forceinline__ bool strip_search(const DevWs& w, const TileCfg& tc, 
         }
       }
 #pragma unroll
-      for (int u = 0; u < kUnroll; ++u) {
-        uint32_t c = kk[u];
-        if (!kWithSelf && i + u == self) c = kKey32Inf;
-        if (tail && i + u >= e) c = kKey32Inf;
-        net_insert(kl, c);
+      for (int u = 0; u < RN; ++u)
+        if (!kWithSelf && i + u == self) kk[u] = kKey32Inf;
+      if (tail) {
+#pragma unroll
+        for (int u = 0; u < RN; ++u)
+          if (i + u >= e) kk[u] = kKey32Inf;
+      }
+      if constexpr (RN == kNetBatch) {
+        sort_batch(kk);
+        merge_batch(kl, kk);
+      } else {
+#pragma unroll
+        for (int u = 0; u < RN; ++u) net_insert(kl, kk[u]);
       }
     };
-    const int full = a + ((e - a) & ~(kUnroll - 1));
-    for (int i = a; i < full; i += kUnroll) round(i, false);
-    if (full < e) round(full, true);
+    if constexpr (RN == kNetBatch) {  // (one copy of the networks: 431 -> 399 us for lists of 31)
+      for (int i = a; i < e; i += RN) round(i, i + RN > e);
+    } else {
+      const int full = a + ((e - a) & ~(RN - 1));
+      for (int i = a; i < full; i += RN) round(i, false);
+      if (full < e) round(full, true);
+    }
     uint32_t key[KT];
     if constexpr (kWithSelf) {
       // the first entry not below the query's own key is that key (it is in
@@ -655,8 +733,8 @@ __device__ __forceinline__ void knn_tile_body(const DevWs& w, const FastCfg& f, 
                                               long long* __restrict__ d2out, const AlignArgs& a,
                                               int tile) {
   // packed 16-bit pairs, or int32 pairs (wide); padded so that a round of
-  // kUnroll reads past a block's last candidate stays inside the buffer
-  __shared__ int2 lpos_store[kPts / 2 + kUnroll];
+  // candidates read past a block's last one stays inside the buffer
+  __shared__ int2 lpos_store[kPts / 2 + kRound<KMAX + 1>];
   __shared__ int lidx[kPts];               // particle index of each staged particle
   __shared__ int s_rbase[kStripRows + 1];  // LDS offset of each halo row
   __shared__ int s_ga0[kStripRows];        // first slot of the row's first piece

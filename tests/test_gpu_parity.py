@@ -552,6 +552,24 @@ def test_knn_staging_capacity(w, part, block, k, cap, over):
     assert np.array_equal(nbr.cpu().numpy(), rn) and np.array_equal(d2.cpu().numpy(), rd)
 
 
+# Long lists take their candidates in sorted batches of 16: rounds that end at,
+# before and after a batch, lists of every compiled length and of fewer.
+@pytest.mark.parametrize("k", [13, 16, 17, 20, 23, 24, 25, 31, 32])
+@pytest.mark.parametrize("n", [34, 47, 48, 49, 63, 64, 65, 257])
+@pytest.mark.parametrize("w", [1 << 10, 1 << 15])
+def test_knn_candidate_batches(w, n, k):
+    box = 16 * w
+    rng = np.random.default_rng(n * 64 + k)
+    x, y = 5 * w + rng.integers(0, w, (2, n)).astype(np.int32)
+    x[-1], y[-1] = x[0], y[0]  # (coincident, and equal distances from the others)
+    ws = nm.Workspace(n, box, w)
+    nm.build_cells(ws, _dev(x, torch.int32), _dev(y, torch.int32))
+    nbr, d2 = nm.knn(ws, k, with_d2=True)
+    assert nm.check(ws) == 0
+    rn, rd = oracle.knn(x, y, box, k)
+    assert np.array_equal(nbr.cpu().numpy(), rn) and np.array_equal(d2.cpu().numpy(), rd)
+
+
 # Searches by a wavefront (no staged strips, few queries a strip): lists that
 # rings 0 to 3 hold and that they don't, grids the rings wrap around, rounds of
 # more candidates than the list, equal distances, exactly k others.
