@@ -385,8 +385,10 @@ __device__ __forceinline__ void strip_tile(const DevWs& w, const MetricCfg& mc, 
 // pass's.  (Separate chunk and wave kernels, and one that reset the lists at
 // the start of every call, took three more launches a call; the last
 // workgroup emptying them, one atomic each on one address, 10 us a pass.)
+// (A workspace without cells, which the strip kernel has reported, may hold
+// anything there and in the tables that the lists are read through.)
 __device__ __forceinline__ bool nothing_listed(const DevWs& w, int ph) {
-  return w.hdr->nchunk[ph] == 0u && w.hdr->ndefer[ph] == 0u;
+  return !ws_ready(w) || (w.hdr->nchunk[ph] == 0u && w.hdr->ndefer[ph] == 0u);
 }
 
 template <class Op>
@@ -883,7 +885,7 @@ __global__ __launch_bounds__(kBlock) void k_metric_fill_rest(DevWs w, MetricCfg 
                                                              int32_t* __restrict__ idx, long long cap) {
   if (nothing_listed(w, 1)) return;  // (so also where nnz > cap, reported by the strip kernel)
   const long long nnz = offsets[w.n];
-  const bool ok = nnz <= cap && nnz >= 0;
+  if (nnz > cap || nnz < 0) return;
   strip_chunks(w, mc, FillOp{offsets, idx, rc2, nnz, key_shift(rc2)});
   const int total = min(w.start[w.C], w.n);
   const int lane = threadIdx.x & 63;
@@ -892,7 +894,7 @@ __global__ __launch_bounds__(kBlock) void k_metric_fill_rest(DevWs w, MetricCfg 
   for_each_deferred(w, 1, [&](int s) {
     const int4 q = w.sorted[s];
     long long base, m;
-    if (!ok || !fill_row(w, offsets, nnz, q.z, base, m) || m == 0) return;
+    if (!fill_row(w, offsets, nnz, q.z, base, m) || m == 0) return;
     int32_t* out = idx + base;
     if (m > kWaveKeys) {
       if (lane == 0 && !global_fill(w, s, rc2, total, m, out)) set_err(w.hdr, NM_E_INVAL);

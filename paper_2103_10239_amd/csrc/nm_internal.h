@@ -117,6 +117,12 @@ __device__ __forceinline__ void set_err(WsHeader* h, int code) {
   if (h) atomicCAS(&h->err, 0, code);
 }
 
+// The workspace holds cells of this grid.
+__device__ __forceinline__ bool cells_built(const DevWs& w) {
+  const WsHeader* hd = w.hdr;
+  return hd->built == kBuilt && hd->n == w.n && hd->box == w.box && hd->cell_w == w.cell_w;
+}
+
 // Signed offset congruent to d modulo L = 2^(32 - sh), in [-L/2, L/2).
 __device__ __forceinline__ int wrap_axis(int d, int sh) {
   return static_cast<int>(static_cast<uint32_t>(d) << sh) >> sh;

@@ -399,11 +399,6 @@ __device__ void write_row(const DevWs& w, const Cell<CAP, BLK, WIDE>& cell, int 
   deg[who] = min(cnt, dmax);
 }
 
-__device__ __forceinline__ bool cells_built(const DevWs& w) {
-  const WsHeader* hd = w.hdr;
-  return hd->built == kBuilt && hd->n == w.n && hd->box == w.box && hd->cell_w == w.cell_w;
-}
-
 // Append slot s to the wide kernel's list (one atomic per wavefront).
 __device__ __forceinline__ void list_wide(const DevWs& w, bool go, int s) {
   const unsigned long long b = __ballot(go);
@@ -478,6 +473,7 @@ __global__ __launch_bounds__(kVwBlock) void k_voronoi_wide(DevWs w, int dmax, in
   __shared__ int sx[kVwCap * kVwBlock];
   __shared__ int sy[kVwCap * kVwBlock];
   __shared__ int sid[kVwCap * kVwBlock];
+  if (!cells_built(w)) return;  // (reported by the narrow kernel; the list may hold anything)
   const int total = min(w.start[w.C], w.n);
   const int nl = static_cast<int>(min<uint32_t>(w.hdr->nvwide, static_cast<uint32_t>(w.n)));
   if (nl == 0) {  // the usual case: no list to empty (512 same-address atomics: 10 us)

@@ -308,7 +308,7 @@ __global__ __launch_bounds__(kBlock) void k_vor_strip(DevWs w, TileCfg tc, int d
   int* lpos = reinterpret_cast<int*>(lpos_store);
   const WsHeader* hd = w.hdr;
   const int tile = xcd_run(blockIdx.x, gridDim.x);
-  if (hd->built != kBuilt || hd->n != w.n || hd->box != w.box || hd->cell_w != w.cell_w) {
+  if (!cells_built(w)) {
     if (tile == 0 && threadIdx.x == 0) set_err(w.hdr, NM_E_INVAL);
     return;
   }
@@ -543,6 +543,7 @@ __global__ __launch_bounds__(64 * kVwWaves) void k_vor_wave(DevWs w, int dmax, i
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int2* off = s_off[wave];
   int* idx = s_idx[wave];
+  if (!cells_built(w)) return;  // (reported by the strip kernel; the list may hold anything)
   const int total = min(w.start[w.C], w.n);
   const int nl = static_cast<int>(min<uint32_t>(w.hdr->nvstale, static_cast<uint32_t>(w.n)));
   const int sh = 32 - w.log2_box, cw = 1 << w.log2_w, gm = w.G - 1;

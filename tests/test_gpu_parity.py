@@ -982,3 +982,23 @@ def test_small_binning_leaves_out_what_is_outside_the_box():
     keep = np.setdiff1d(np.arange(n), [3, 500])
     rn, _ = oracle.knn(x[keep], y[keep], L, 3)
     assert np.array_equal(nbr.cpu().numpy()[keep], keep[rn])
+
+
+# A workspace without cells may hold anything: a call reports it and follows no
+# list that its header seems to count (header words 5: built, 6 and 7: deferred
+# rows of the count and the fill, 8 and 9: chunks).
+def test_metric_list_without_cells_is_refused_whatever_the_lists_hold():
+    n = 1000
+    x, y, _ = workloads.uniform(n)
+    ws = nm.Workspace(n, L, L // 16)
+    nm.build_cells(ws, _dev(x, torch.int32), _dev(y, torch.int32))
+    h = ws.buf[:256].view(torch.int32)
+    for words in ((6, 7), (8, 9)):
+        h[5] = 0
+        h[list(words)] = 7
+        offs = torch.zeros(n + 1, dtype=torch.int32, device="cuda")
+        idx = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+        nm.metric_list(ws, (L // 8) ** 2, offs, idx)
+        assert nm.check(ws) == nm.NM_E_INVAL
+        assert (offs == 0).all() and (idx == -7).all()
+        h[list(words)] = 0

@@ -544,3 +544,24 @@ def test_voronoi_forces_reject_inconsistent_rows():
     nm.voronoi_forces(_dev(x, torch.int32), _dev(y, torch.int32), box, _dev(ring, torch.int32),
                       _dev(deg, torch.int32), ws=ws, **_vm_args(n, box))
     assert nm.check(ws) == nm.NM_E_INVAL
+
+
+# A workspace without cells may hold anything: a call reports it and follows no
+# list that its header seems to count (header words 5: built, 10: cells for the
+# 64-bit kernel, 12: rows for the wave and general kernels).
+def test_rows_without_cells_are_refused_whatever_the_lists_hold():
+    n, box, w = 1000, 1 << 16, 1 << 11
+    x, y, _ = workloads.uniform(n, box=box)
+    X, Y = _dev(x, torch.int32), _dev(y, torch.int32)
+    ws = nm.Workspace(n, box, w)
+    nm.build_cells(ws, X, Y)
+    ring, deg = nm.voronoi(ws, 16)
+    assert nm.check(ws) == 0
+    h = ws.buf[:256].view(torch.int32)
+    for word in (10, 12):
+        h[5], h[word] = 0, 7
+        R, D = torch.full_like(ring, -7), torch.full_like(deg, -7)
+        nm.voronoi(ws, 16, R, D)
+        assert nm.check(ws) == nm.NM_E_INVAL
+        assert (R == -7).all() and (D == -7).all()
+        h[word] = 0
