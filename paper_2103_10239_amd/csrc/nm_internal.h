@@ -13,7 +13,7 @@
 //   dflag       uint8[n]     1 for a slot whose k-NN search is deferred (kept 0
 //                            between launches)
 //   chunks      int4[cap]    row chunks of dense metric strips, cap = n / 32 + 1024;
-//                            the Voronoi reuse test's per-workgroup failures and areas
+//                            the Voronoi update's per-workgroup failures and areas
 //   vlist       int32[n]     slots of Voronoi cells handed to the 64-bit kernel
 //   coarse      int4[n]      particles in coarse-bin order (two-level binning)
 //   hist        int32[nbins * nblk + 1]  per-workgroup coarse-bin counts, then
@@ -64,7 +64,8 @@ struct WsHeader {
   uint32_t pad0;
   int64_t off_start;   // bytes from here to start and sorted, for calls that get
   int64_t off_sorted;  // the workspace without its grid
-  int32_t pad[42];
+  unsigned long long varea2;  // sum over Voronoi rows of a_t x a_{t+1} (the reuse test alone)
+  int32_t pad[40];
 };
 static_assert(sizeof(WsHeader) == 256, "header is one 256-byte block");
 

@@ -539,7 +539,11 @@ __global__ __launch_bounds__(kBlock) void k_vor_clear(WsHeader* hdr, uint8_t* __
   if (again && hdr->nvgo == 0u) return;
   const int i = blockIdx.x * kBlock + threadIdx.x;
   if (i < n) stale[i] = 0;
-  if (i == 0) hdr->nvstale = 0u;
+  if (i == 0) {
+    hdr->nvstale = 0u;
+    hdr->nvfail = 0u;
+    hdr->varea2 = 0ull;
+  }
 }
 
 // Rows of up to this many entries are read whole when searched.
@@ -928,10 +932,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
   WsHeader* hdr = w.hdr;
   if (again && hdr->nvgo == 0u) return;
   if (kOrdered && !cells_built(w)) {
-    if (threadIdx.x == 0) {
-      if (blockIdx.x == 0) set_err(hdr, NM_E_INVAL);
-      w.chunks[blockIdx.x] = make_int4(0, 0, 0, 0);
-    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) set_err(hdr, NM_E_INVAL);
     return;
   }
   const int n = w.n, log2_box = w.log2_box;
@@ -958,10 +959,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
       }
     }
   }
-  // The workgroup's failures and area (that counts only while no row fails)
-  // go to its entry of the metric lists' chunk table, which is free between
-  // their calls; k_vor_total adds them up (an atomic per wavefront and counter
-  // on one address each: 580 us for the first round at 2^20, 440 without).
+  // The workgroup's failures and area (that counts only while no row fails).
+  // In the cells' order they go to its entry of the metric lists' chunk table,
+  // which is free between their calls; k_vor_total adds them up (an atomic per
+  // wavefront and counter on one address each: 580 us for the first round at
+  // 2^20, 440 without).  The test alone is given a workspace for its counters
+  // only, which may hold another grid or none: an atomic each per workgroup.
   __shared__ long long s_area[kBlock / 64];
   __shared__ int s_fail[kBlock / 64];
   const int nf = __popcll(__ballot(fail));
@@ -980,7 +983,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
       a += s_area[q];
       f += s_fail[q];
     }
-    w.chunks[blockIdx.x] = make_int4(static_cast<int>(a), static_cast<int>(a >> 32), f, 0);
+    if (kOrdered) {
+      w.chunks[blockIdx.x] = make_int4(static_cast<int>(a), static_cast<int>(a >> 32), f, 0);
+    } else {
+      if (f != 0) atomicAdd(&hdr->nvfail, static_cast<uint32_t>(f));
+      if (a != 0) atomicAdd(&hdr->varea2, static_cast<unsigned long long>(a));
+    }
   }
 }
 
@@ -1033,8 +1041,9 @@ __global__ __launch_bounds__(kBlock) void k_vor_list(DevWs w, const uint8_t* __r
   if (go && at < static_cast<uint32_t>(w.n)) w.rank[at] = s;
 }
 
-// After k_vor_check (nb workgroups): how many rows failed; a total area other
-// than 6 L^2 distrusts every row.  The update's later rounds run while rows
+// After k_vor_check (nb workgroups' entries in the chunk table, or none: the
+// header's counters): how many rows failed; a total area other than 6 L^2
+// distrusts every row.  The update's later rounds run while rows
 // fail (nvgo).  One workgroup; the counts and areas are integers, so their
 // order does not matter.
 //
@@ -1050,6 +1059,14 @@ constexpr uint32_t kVorFull = 512;
 __global__ __launch_bounds__(kBlock) void k_vor_total(DevWs w, int nb, int32_t* out, int again, int full) {
   WsHeader* hdr = w.hdr;
   if (again && hdr->nvgo == 0u) return;
+  if (nb > 0 && !cells_built(w)) {  // (reported by the check, which ran nothing)
+    if (threadIdx.x == 0) {
+      hdr->nvgo = 0u;
+      hdr->nvfull = 0u;
+      if (out) *out = 0x7FFFFFFF;
+    }
+    return;
+  }
   __shared__ unsigned long long s_area[kBlock];
   __shared__ uint32_t s_fail[kBlock];
   unsigned long long area = 0;
@@ -1072,8 +1089,8 @@ __global__ __launch_bounds__(kBlock) void k_vor_total(DevWs w, int nb, int32_t* 
   }
   if (threadIdx.x != 0) return;
   const unsigned long long want = 6ull << (2 * w.log2_box);
-  uint32_t nf = s_fail[0];
-  if (nf == 0u && s_area[0] != want) nf = 0x80000000u;
+  uint32_t nf = s_fail[0] + (nb > 0 ? 0u : hdr->nvfail);
+  if (nf == 0u && s_area[0] + (nb > 0 ? 0ull : hdr->varea2) != want) nf = 0x80000000u;
   hdr->nvfail = nf;
   hdr->nvgo = nf != 0u ? 1u : 0u;
   hdr->nvfull = full && static_cast<unsigned long long>(nf) * kVorFull > static_cast<unsigned long long>(w.n) ? 1u : 0u;
@@ -1112,7 +1129,7 @@ hipError_t launch_voronoi_check(const DevWs& w, const int32_t* x, const int32_t*
   const int nb = (w.n + kBlock - 1) / kBlock;
   hipLaunchKernelGGL(k_vor_clear, dim3(nb), dim3(kBlock), 0, s, w.hdr, stale, w.n, 0);
   hipLaunchKernelGGL(k_vor_check<false>, dim3(nb), dim3(kBlock), 0, s, x, y, w, dmax, ring, deg, stale, nullptr, 0);
-  hipLaunchKernelGGL(k_vor_total, dim3(1), dim3(kBlock), 0, s, w, nb, nfail, 0, 0);
+  hipLaunchKernelGGL(k_vor_total, dim3(1), dim3(kBlock), 0, s, w, 0, nfail, 0, 0);
   return hipGetLastError();
 }
 

@@ -565,3 +565,31 @@ def test_rows_without_cells_are_refused_whatever_the_lists_hold():
         assert nm.check(ws) == nm.NM_E_INVAL
         assert (R == -7).all() and (D == -7).all()
         h[word] = 0
+
+
+# The reuse test uses a workspace for its counters only: one of another grid, or
+# one never prepared, does, and nothing beyond the 256 bytes of its header is
+# written.  The update needs cells, refuses a workspace without, and leaves it alone.
+@pytest.mark.parametrize("of", ["this grid", "another grid", "nothing"])
+@pytest.mark.parametrize("moved", [0, 40])
+def test_check_needs_the_workspace_header_only(of, moved):
+    n, box, w = 4096, 1 << 16, 1 << 11
+    x, y, _ = workloads.uniform(n, box=box)
+    ring, deg, st, good = _gpu_rows(x, y, box, w)
+    assert st == 0
+    x1 = ((x + np.random.default_rng(2).integers(-moved, moved + 1, n)) % box).astype(np.int32)
+    R, D, X1, Y1 = _dev(ring, torch.int32), _dev(deg, torch.int32), _dev(x1, torch.int32), _dev(y, torch.int32)
+    stale, nfail = nm.voronoi_check(good, X1, Y1, R, D)
+    assert (int(nfail.item()) > 0) == (moved > 0)
+    ws = nm.Workspace(300, box, w, nbytes=good.nbytes) if of == "another grid" else nm.Workspace(n, box, w)
+    ws.grid = good.grid
+    ws.buf[0 if of == "nothing" else 256:] = 0x5A
+    ws.buf[4:8] = 0  # (the error word)
+    s2, f2 = nm.voronoi_check(ws, X1, Y1, R, D)
+    assert nm.check(ws) == 0
+    assert torch.equal(stale, s2) and torch.equal(nfail, f2)
+    assert (ws.buf[256:] == 0x5A).all()
+    nm.voronoi_update(ws, X1, Y1, R, D)
+    assert nm.check(ws) == nm.NM_E_INVAL
+    assert (ws.buf[256:] == 0x5A).all()
+    assert np.array_equal(R.cpu().numpy(), ring) and np.array_equal(D.cpu().numpy(), deg)
