@@ -59,7 +59,13 @@ constexpr int kVnCap = 16;     // cell edges, narrow kernel (power of two)
 constexpr int kVnSpan = 1 << 14;
 constexpr int kVwBlock = 64;   // lanes per workgroup, wide kernel
 constexpr int kVwCap = 64;     // cell edges, wide kernel (power of two)
-constexpr int kVwGrid = 512;   // workgroups of the wide kernel
+// The wide kernel's rows are chains of rings and clippings of their own lengths,
+// so a wavefront takes as few of the list as the waves that the device holds
+// allow, at most kVwRows (their columns bound the waves: 12 KB each).  Rows of
+// 65,536 particles in 256 clusters: 39 ms with 64 rows a wavefront, 12 with
+// as few of 64 as 768 waves allow, 12 with 16; of 2^20: 336, 142 and 107 ms.
+constexpr int kVwRows = 16;
+constexpr int kVwGrid = 256 * (160 / (kVwCap * kVwRows * 12 / 1024));  // workgroups of the wide kernel
 
 // ---------------------------------------------------------------------------
 // exact predicates
@@ -415,11 +421,22 @@ __device__ __forceinline__ void list_wide(const DevWs& w, bool go, int s) {
 // Narrow kernel over slots: every slot (list == nullptr) or the slots listed
 // in `list` (count at *count), with `flagged` only those whose dflag is set
 // (and cleared here).  With `gate`, nothing runs unless *gate != 0.
+//
+// The rows that the strip and wave kernels leave are flagged and taken in slot
+// order: lanes of a wavefront then walk the same cells, where the strips' list
+// mixes them (262,144 particles, most of them in 64 tight clusters: 24-29 ms in
+// the list's order, 16 in slot order).  Where the update rebuilds every row
+// (nvfull), those not marked in `stale` passed the reuse test and are kept
+// instead: these kernels are the slow ones (and may not take such a row: its
+// cell may reach L/8), and the update tests the rows again.  The general kernels'
+// share of that update 23.5 ms with every row built, 18 with those kept; of
+// 65,536 particles in 256 clusters 11.9 and 3.9.
 __global__ __launch_bounds__(kVnBlock) void k_voronoi(DevWs w, int dmax, int32_t* __restrict__ ring,
                                                       int32_t* __restrict__ deg,
                                                       const int32_t* __restrict__ list,
                                                       const uint32_t* __restrict__ count, int flagged,
-                                                      const uint32_t* __restrict__ gate) {
+                                                      const uint32_t* __restrict__ gate,
+                                                      const uint8_t* __restrict__ stale) {
   __shared__ int sxy[kVnCap * kVnBlock];
   __shared__ int sid[kVnCap * kVnBlock];
   if (gate && *gate == 0u) return;
@@ -439,6 +456,10 @@ __global__ __launch_bounds__(kVnBlock) void k_voronoi(DevWs w, int dmax, int32_t
   if (go && flagged) {
     go = w.dflag[s] != 0;
     if (go) w.dflag[s] = 0;
+    if (go && stale && w.hdr->nvfull != 0u && stale[w.sorted[s].z] == 0) {
+      go = false;
+      w.hdr->nvkeep = 1u;
+    }
   }
   if (go) {
     const int4 e = w.sorted[s];
@@ -455,7 +476,7 @@ __global__ __launch_bounds__(kVnBlock) void k_voronoi(DevWs w, int dmax, int32_t
 __device__ __forceinline__ void general_done(WsHeader* h) {
   h->nvstale = 0u;  // (the narrow kernel's list)
   if (h->nvfull != 0u) {
-    const uint32_t kept = atomicOr(&h->nvkeep, 0u);
+    const uint32_t kept = h->nvkeep;
     h->nvfail = kept;
     h->nvgo = kept;
     h->nvfull = 0u;
@@ -464,15 +485,11 @@ __device__ __forceinline__ void general_done(WsHeader* h) {
 }
 
 // Wide kernel over the listed slots; the last workgroup empties the list.
-// Where the update rebuilds every row (nvfull), rows not marked in `stale`
-// passed the reuse test: one that cannot be built (its cell reaches L/8) is
-// kept without an error, and the update tests the rows again.
 __global__ __launch_bounds__(kVwBlock) void k_voronoi_wide(DevWs w, int dmax, int32_t* __restrict__ ring,
-                                                           int32_t* __restrict__ deg,
-                                                           const uint8_t* __restrict__ stale) {
-  __shared__ int sx[kVwCap * kVwBlock];
-  __shared__ int sy[kVwCap * kVwBlock];
-  __shared__ int sid[kVwCap * kVwBlock];
+                                                           int32_t* __restrict__ deg) {
+  __shared__ int sx[kVwCap * kVwRows];
+  __shared__ int sy[kVwCap * kVwRows];
+  __shared__ int sid[kVwCap * kVwRows];
   if (!cells_built(w)) return;  // (reported by the narrow kernel; the list may hold anything)
   const int total = min(w.start[w.C], w.n);
   const int nl = static_cast<int>(min<uint32_t>(w.hdr->nvwide, static_cast<uint32_t>(w.n)));
@@ -480,19 +497,14 @@ __global__ __launch_bounds__(kVwBlock) void k_voronoi_wide(DevWs w, int dmax, in
     if (blockIdx.x == 0 && threadIdx.x == 0) general_done(w.hdr);
     return;
   }
-  const bool full = stale && w.hdr->nvfull != 0u;
-  for (int k = blockIdx.x * kVwBlock + threadIdx.x; k - threadIdx.x < nl; k += gridDim.x * kVwBlock) {
-    if (k >= nl) continue;
+  const int per = min(kVwRows, (nl + static_cast<int>(gridDim.x) - 1) / static_cast<int>(gridDim.x));
+  for (int k0 = blockIdx.x * per; k0 < nl; k0 += gridDim.x * per) {
+    const int k = k0 + threadIdx.x;
+    if (static_cast<int>(threadIdx.x) >= per || k >= nl) continue;
     const int s = w.vlist[k];
     const int4 e = w.sorted[s];
-    Cell<kVwCap, kVwBlock, true> cell{sx + threadIdx.x, sy + threadIdx.x, sid + threadIdx.x, 0, 0};
-    DevWs v = w;
-    const bool keep = full && stale[e.z] == 0;
-    if (keep) v.hdr = nullptr;  // (no error from build_cell)
-    if (build_cell(v, cell, s, e.x, e.y, total) == kCellDone)
-      write_row(w, cell, e.z, e.x, e.y, total, dmax, ring, deg);
-    else if (keep)
-      atomicOr(&w.hdr->nvkeep, 1u);
+    Cell<kVwCap, kVwRows, true> cell{sx + threadIdx.x, sy + threadIdx.x, sid + threadIdx.x, 0, 0};
+    if (build_cell(w, cell, s, e.x, e.y, total) == kCellDone) write_row(w, cell, e.z, e.x, e.y, total, dmax, ring, deg);
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -1101,15 +1113,19 @@ __global__ __launch_bounds__(kBlock) void k_vor_total(DevWs w, int nb, int32_t* 
 
 namespace {
 
-// The general kernels over the listed slots (rank, nvstale; those whose dflag
-// is set with `flagged`), or over every slot when `every`; nothing runs when
-// `gate` is given and *gate is 0.
+// The general kernels over the listed slots (rank, nvstale), or over every slot
+// when `every`, or over those that the wave kernel flagged with `flagged`;
+// nothing runs when `gate` is given and *gate is 0.
 hipError_t launch_general(const DevWs& w, int dmax, int32_t* ring, int32_t* deg, bool every, bool flagged,
                           const uint32_t* gate, const uint8_t* stale, hipStream_t s) {
   const int nb = (w.n + kVnBlock - 1) / kVnBlock;
-  hipLaunchKernelGGL(k_voronoi, dim3(nb), dim3(kVnBlock), 0, s, w, dmax, ring, deg, every ? nullptr : w.rank,
-                     every ? nullptr : &w.hdr->nvstale, flagged ? 1 : 0, gate);
-  hipLaunchKernelGGL(k_voronoi_wide, dim3(kVwGrid), dim3(kVwBlock), 0, s, w, dmax, ring, deg, stale);
+  if (flagged)
+    hipLaunchKernelGGL(k_voronoi, dim3(nb), dim3(kVnBlock), 0, s, w, dmax, ring, deg, nullptr, nullptr, 1,
+                       &w.hdr->nvstale, stale);
+  else
+    hipLaunchKernelGGL(k_voronoi, dim3(nb), dim3(kVnBlock), 0, s, w, dmax, ring, deg, every ? nullptr : w.rank,
+                       every ? nullptr : &w.hdr->nvstale, 0, gate, nullptr);
+  hipLaunchKernelGGL(k_voronoi_wide, dim3(kVwGrid), dim3(kVwBlock), 0, s, w, dmax, ring, deg);
   return hipGetLastError();
 }
 

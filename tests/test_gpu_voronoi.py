@@ -593,3 +593,24 @@ def test_check_needs_the_workspace_header_only(of, moved):
     assert nm.check(ws) == nm.NM_E_INVAL
     assert (ws.buf[256:] == 0x5A).all()
     assert np.array_equal(R.cpu().numpy(), ring) and np.array_equal(D.cpu().numpy(), deg)
+
+
+# Updates of states that the strips leave much of to the other kernels (dense
+# clumps, coincident particles, offsets of more than 16 bits): every row built
+# again where many fail, those left by the strips and passing the test kept.
+@pytest.mark.parametrize("box,w", [(1 << 14, 1 << 8), (1 << 14, 1 << 11), (1 << 20, 1 << 14), (1 << 20, 1 << 17)])
+@pytest.mark.parametrize("move", [1, 6])
+def test_update_of_clumped_states_matches_oracle(box, w, move):
+    x, y = _clump(900, 1100, box, min(w, 1 << 14))
+    n = len(x)
+    rng = np.random.default_rng(move)
+    x1 = ((x + rng.integers(-move, move + 1, n)) % box).astype(np.int32)
+    y1 = ((y + rng.integers(-move, move + 1, n)) % box).astype(np.int32)
+    ring, deg, st, ws = _gpu_rows(x, y, box, w, dmax=64)
+    assert st == 0
+    R, D, X1, Y1 = _dev(ring, torch.int32), _dev(deg, torch.int32), _dev(x1, torch.int32), _dev(y1, torch.int32)
+    nm.build_cells(ws, X1, Y1)
+    nfail = int(nm.voronoi_update(ws, X1, Y1, R, D).item())
+    assert nm.check(ws) == 0
+    assert nfail * 512 > n
+    assert _rows_of(R.cpu().numpy(), D.cpu().numpy()) == _oracle_rows(x1, y1, box)
