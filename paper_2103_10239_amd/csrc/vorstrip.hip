@@ -55,40 +55,67 @@ __device__ __forceinline__ int dot2(int a, int b) {
   return r;
 }
 
-// The step from neighbour a in exact integers, over candidates [b, e).
-// (pq, pqy), (pa, pay): packed positions of the query and of a (narrow), or x, y.
+// t of candidate c in the step from neighbour a, within 2^-20.4 of itself;
+// infinite where c is not on the left of a.  (pq, pqy), (pa, pay): packed
+// positions of the query and of a (narrow, with perp = perp(a)), or x, y.
+// Wide: fp32 offsets are exact (below 2^24); a sum or difference of two products
+// with the rounding of one put back is within 2^-23 of itself, and zero only
+// where it is zero.
+template <bool kWide>
+struct PivotStep {
+  int pq, pqy, pa, perp;
+  float axf, ayf;
+  __device__ __forceinline__ PivotStep(int pq_, int pqy_, int pa_, int ax, int ay)
+      : pq(pq_), pqy(pqy_), pa(pa_), perp(pack_rel(-ay, ax)), axf(static_cast<float>(ax)), ayf(static_cast<float>(ay)) {}
+  __device__ __forceinline__ float t(int2 c) const {
+    const float cx = static_cast<float>(c.x - pq), cy = static_cast<float>(c.y - pqy);
+    const float ex = cx - axf, ey = cy - ayf;
+    const float p = cy * ey, q = ayf * cx;
+    const float num = fmaf(cx, ex, p) + fmaf(cy, ey, -p);
+    const float den = fmaf(axf, cy, -q) - fmaf(ayf, cx, -q);
+    const float v = num * __builtin_amdgcn_rcpf(den);
+    return den > 0.0f ? v : INFINITY;
+  }
+  __device__ __forceinline__ float t(int c) const {
+    const short2v d = __builtin_bit_cast(short2v, c) - __builtin_bit_cast(short2v, pq);
+    const short2v f = __builtin_bit_cast(short2v, c) - __builtin_bit_cast(short2v, pa);
+    const int num = dot2(__builtin_bit_cast(int, d), __builtin_bit_cast(int, f));
+    const int den = dot2(__builtin_bit_cast(int, d), perp);
+    const float q = static_cast<float>(num) * __builtin_amdgcn_rcpf(static_cast<float>(den));
+    return den > 0 ? q : INFINITY;
+  }
+};
+
+// The step from neighbour (ax, ay) in exact integers: of the candidates [b, e),
+// those whose t is not above `lim` (twice the error above the smallest) decide.
+// They are collected by a pass like the step's own, over the rows of cells that
+// the circle found meets, and then compared, the lanes' first, second, ... ones
+// together: 2^20 particles on a square lattice 254 us (375 with every candidate
+// of the block compared in integers, 249 by clipping alone), 2^18 on one a few
+// units out of place 264 (500, 362).
 // Returns the neighbour's LDS index, -1: none, -2: two particles at its position.
 template <bool kWide>
-__device__ __noinline__ int vor_pivot_exact(const int* lpos, int b, int e, int pq, int pqy, int pa, int pay) {
+__device__ __noinline__ int vor_pivot_exact(const int* lpos, int b, int e, int pq, int pqy, int pa, int ax, int ay,
+                                            float lim) {
   using I = std::conditional_t<kWide, __int128, long long>;
-  long long ax, ay;
-  auto offset = [&](int i, long long& ox, long long& oy) {
-    if (kWide) {
-      const int2 c = reinterpret_cast<const int2*>(lpos)[i];
-      ox = c.x - pq;
-      oy = c.y - pqy;
-    } else {
-      const short2v d = __builtin_bit_cast(short2v, lpos[i]) - __builtin_bit_cast(short2v, pq);
-      ox = d[0];
-      oy = d[1];
-    }
-  };
-  if (kWide) {
-    ax = pa - pq;
-    ay = pay - pqy;
-  } else {
-    const short2v d = __builtin_bit_cast(short2v, pa) - __builtin_bit_cast(short2v, pq);
-    ax = d[0];
-    ay = d[1];
-  }
+  using P = std::conditional_t<kWide, int2, int>;
+  const P* pos = reinterpret_cast<const P*>(lpos);
+  const PivotStep<kWide> step(pq, pqy, pa, ax, ay);
   int best = -1;
   bool twin = false;
   long long bn = 0, bd = 1, bx = 0, by = 0;
-  for (int i = b; i < e; ++i) {
+  auto compare = [&](int i) {
     long long cx, cy;
-    offset(i, cx, cy);
+    if constexpr (kWide) {
+      cx = pos[i].x - pq;
+      cy = pos[i].y - pqy;
+    } else {
+      const short2v d = __builtin_bit_cast(short2v, pos[i]) - __builtin_bit_cast(short2v, pq);
+      cx = d[0];
+      cy = d[1];
+    }
     const long long den = ax * cy - ay * cx;
-    if (den <= 0) continue;
+    if (den <= 0) return;
     const long long num = cx * (cx - ax) + cy * (cy - ay);
     const I diff = static_cast<I>(num) * bd - static_cast<I>(bn) * den;
     bool take = best < 0 || diff < 0;
@@ -106,18 +133,39 @@ __device__ __noinline__ int vor_pivot_exact(const int* lpos, int b, int e, int p
       bx = cx;
       by = cy;
     }
+  };
+  unsigned long long near = 0ull;
+  int count = 0;
+  for (int i0 = b; i0 < e; i0 += kUnroll) {
+    P c[kUnroll];
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) c[u] = pos[i0 + u];  // (buffer padded by kUnroll)
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+      if (i0 + u < e && step.t(c[u]) <= lim) {
+        if (count < 4) near |= static_cast<unsigned long long>(i0 + u) << (16 * count);
+        ++count;
+      }
+    }
+  }
+  if (count <= 4) {
+    for (int j = 0; j < count; ++j) compare(static_cast<int>(near >> (16 * j)) & 0xFFFF);
+  } else {
+    for (int i = b; i < e; ++i) compare(i);
   }
   return twin ? -2 : best;
 }
 
-// The star of staged particle `self` over the candidates [b, e) of its block,
-// whose outside lies at offsets <= -gl or >= gr in x, <= -gd or >= gu in y.
+// The star of staged particle `self` over the candidates of its block, whose rows
+// of cells start at rows[0], rows[1], ... and whose outside lies at offsets
+// <= -gl or >= gr in x, <= -gd or >= gu in y.
 // Writes the neighbours' LDS indices to col[0 .. m) (stride kBlock),
 // counter-clockwise from the nearest; first: the entry to start the row at
 // (counter-clockwise from +x).  Returns m, or 0 when the row is not certain.
 template <bool kWide>
-__device__ __forceinline__ int vor_star(const int* lpos, int b, int e, int self, int gl, int gr, int gd,
+__device__ __forceinline__ int vor_star(const int* lpos, const int* rows, int lw, int self, int gl, int gr, int gd,
                                         int gu, int cap, float domain, uint16_t* col, int& first) {
+  const int b = rows[0], e = rows[(gd + gu - 1) >> lw];
   const int2* lpos2 = reinterpret_cast<const int2*>(lpos);
   int pq, pqy = 0;
   if (kWide) {
@@ -171,12 +219,11 @@ __device__ __forceinline__ int vor_star(const int* lpos, int b, int e, int self,
     if (m >= cap) return 0;
     col[m * kBlock] = static_cast<uint16_t>(cur);
     ++m;
-    int pa, pay = 0, ax, ay;
+    int pa, ax, ay;
     if (kWide) {
       pa = lpos2[cur].x;
-      pay = lpos2[cur].y;
       ax = pa - pq;
-      ay = pay - pqy;
+      ay = lpos2[cur].y - pqy;
     } else {
       pa = lpos[cur];
       const short2v d = __builtin_bit_cast(short2v, pa) - __builtin_bit_cast(short2v, pq);
@@ -185,41 +232,19 @@ __device__ __forceinline__ int vor_star(const int* lpos, int b, int e, int self,
     }
     float t0 = INFINITY, t1 = INFINITY;  // the two smallest t
     int next = -1;
-    const int perp = pack_rel(-ay, ax);  // (narrow) a x c = c . perp
-    const float axf = static_cast<float>(ax), ayf = static_cast<float>(ay);
+    const PivotStep<kWide> step(pq, pqy, pa, ax, ay);
     auto round = [&](int i, bool tail) {
       float t[kUnroll];
-      if (kWide) {
-        int2 c[kUnroll];
+      std::conditional_t<kWide, int2, int> c[kUnroll];
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) c[u] = lpos2[i + u];
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-          // fp32 offsets are exact (below 2^24); a sum or difference of two
-          // products with the rounding of one put back is within 2^-23 of
-          // itself, and zero only where it is zero
-          const float cx = static_cast<float>(c[u].x - pq), cy = static_cast<float>(c[u].y - pqy);
-          const float ex = cx - axf, ey = cy - ayf;
-          const float p = cy * ey, q = ayf * cx;
-          const float num = fmaf(cx, ex, p) + fmaf(cy, ey, -p);
-          const float den = fmaf(axf, cy, -q) - fmaf(ayf, cx, -q);
-          const float v = num * __builtin_amdgcn_rcpf(den);
-          t[u] = den > 0.0f ? v : INFINITY;
-        }
-      } else {
-        int c[kUnroll];
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) c[u] = lpos[i + u];
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-          const short2v d = __builtin_bit_cast(short2v, c[u]) - __builtin_bit_cast(short2v, pq);
-          const short2v f = __builtin_bit_cast(short2v, c[u]) - __builtin_bit_cast(short2v, pa);
-          const int num = dot2(__builtin_bit_cast(int, d), __builtin_bit_cast(int, f));
-          const int den = dot2(__builtin_bit_cast(int, d), perp);
-          const float q = static_cast<float>(num) * __builtin_amdgcn_rcpf(static_cast<float>(den));
-          t[u] = den > 0 ? q : INFINITY;
-        }
+      for (int u = 0; u < kUnroll; ++u) {
+        if constexpr (kWide)
+          c[u] = lpos2[i + u];
+        else
+          c[u] = lpos[i + u];
       }
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) t[u] = step.t(c[u]);
 #pragma unroll
       for (int u = 0; u < kUnroll; ++u) {
         const float v = tail && i + u >= e ? INFINITY : t[u];
@@ -232,10 +257,6 @@ __device__ __forceinline__ int vor_star(const int* lpos, int b, int e, int self,
     for (int i = b; i < full; i += kUnroll) round(i, false);
     if (full < e) round(full, true);
     if (next < 0) return 0;
-    if (t1 - t0 <= (fabsf(t0) + fabsf(t1)) * 0x1p-19f) {
-      next = vor_pivot_exact<kWide>(lpos, b, e, pq, pqy, pa, pay);
-      if (next < 0) return 0;
-    }
     // the circle through 0, a and the neighbour lies inside the block, its
     // centre inside the domain (fp32: a few 2^-22 of the radius, well under
     // the margin)
@@ -245,6 +266,14 @@ __device__ __forceinline__ int vor_star(const int* lpos, int b, int e, int self,
     if (!(r < domain && hx - r > static_cast<float>(-gl) && hx + r < static_cast<float>(gr) &&
           hy - r > static_cast<float>(-gd) && hy + r < static_cast<float>(gu)))
       return 0;
+    if (t1 - t0 <= (fabsf(t0) + fabsf(t1)) * 0x1p-19f) {
+      // what may be nearer lies on that circle: in the rows of cells that it meets
+      const int top = ((gd + gu - 1) >> lw) - 1;
+      const int lo = max(static_cast<int>(hy - r + static_cast<float>(gd - 1)) >> lw, 0);
+      const int hi = min(static_cast<int>(hy + r + static_cast<float>(gd)) >> lw, top);
+      next = vor_pivot_exact<kWide>(lpos, rows[lo], rows[hi + 1], pq, pqy, pa, ax, ay, t0 + fabsf(t0) * 0x1p-19f);
+      if (next < 0) return 0;
+    }
     int bx, by;
     if (kWide) {
       bx = lpos2[next].x - pq;
@@ -410,10 +439,9 @@ __global__ __launch_bounds__(kBlock) void k_vor_strip(DevWs w, TileCfg tc, int d
             const int cw = 1 << lw;
             const int gl = rx + 1, gr = W * cw - rx;
             const int gd = oy + half * cw + 1, gu = (half + 1) * cw - oy;
-            const int b = s_rbase[cy - half], e = s_rbase[cy + half + 1];
             int first = 0;
             uint16_t* col = s_col + threadIdx.x;
-            const int m = vor_star<kWide>(lpos, b, e, self, gl, gr, gd, gu, cap, domain, col, first);
+            const int m = vor_star<kWide>(lpos, s_rbase + cy - half, lw, self, gl, gr, gd, gu, cap, domain, col, first);
             if (m > 0) {
               const int who = lidx[self];
               int32_t* row = ring + static_cast<int64_t>(who) * dmax;

@@ -614,3 +614,29 @@ def test_update_of_clumped_states_matches_oracle(box, w, move):
     assert nm.check(ws) == 0
     assert nfail * 512 > n
     assert _rows_of(R.cpu().numpy(), D.cpu().numpy()) == _oracle_rows(x1, y1, box)
+
+
+# Equal and nearly equal circle parameters on strips: lattices whose particles
+# are all co-circular in fours, or are up to a few units out of place, in
+# wide and narrow strips, and rings of particles on one circle (up to 12 ties a step).
+@pytest.mark.parametrize("jitter", [0, 1, 2])
+@pytest.mark.parametrize("rings,box,w", [(True, 1 << 14, 1 << 8), (True, 1 << 20, 1 << 14), (False, 1 << 16, 1 << 9),
+                                         (False, 1 << 20, 1 << 14)])
+def test_voronoi_strips_near_ties(rings, box, w, jitter):
+    x, y, a = workloads.lattice(64, box=box)
+    x, y = x.astype(np.int64), y.astype(np.int64)
+    if rings:  # nothing inside the circle through the twelve lattice points at distance 5 of some
+        keep = np.ones(len(x), bool)
+        for c in range(0, len(x), 650):
+            d = (x // a - x[c] // a + 32) % 64 - 32, (y // a - y[c] // a + 32) % 64 - 32
+            r2 = d[0] ** 2 + d[1] ** 2
+            keep &= (r2 >= 25) | (r2 == 0)
+        x, y = x[keep], y[keep]
+    rng = np.random.default_rng(jitter)
+    x = ((x + rng.integers(-jitter, jitter + 1, len(x))) % box).astype(np.int32)
+    y = ((y + rng.integers(-jitter, jitter + 1, len(y))) % box).astype(np.int32)
+    ring, deg, st, _ = _gpu_rows(x, y, box, w, dmax=32)
+    assert st == 0
+    some = np.arange(0, len(x), 8, dtype=np.int32)
+    got = _rows_of(ring, deg)
+    assert [got[i] for i in some] == _oracle_rows(x, y, box, rows=some)
