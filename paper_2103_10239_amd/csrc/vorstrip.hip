@@ -17,15 +17,16 @@
 // candidate is a serial chain of exact predicates with its own path per lane.
 //
 // Exactness.  c.(c - a) and a x c are exact integers (16-bit offsets) or
-// within 2^-23 of them; t is their fp32 quotient, within 2^-20.4 of itself.  Where the two smallest quotients lie
-// within 2^-19 of each other the step is decided again in exact integers
-// (cross-multiplied); equal values are co-circular particles, of which the
-// last counter-clockwise is the neighbour (the others' cells only touch).
-// A row is written only when every circle of its star lies inside the block
-// (with a margin above the rounding of its centre and radius) and its centre
-// within L/8: no particle outside the block can then change it.  Everything
-// else -- circles that reach out of the block, coincident particles, rows
-// longer than 16 or dmax, strips that could not be staged -- is listed for
+// within 2^-23 of them; t is their fp32 quotient, within 2^-20.4 of itself.
+// Where the two smallest quotients lie within 2^-19 of each other the step is
+// decided again in exact integers (cross-multiplied); equal values are
+// co-circular particles, of which the last counter-clockwise is the neighbour
+// (the others' cells only touch), or particles that share a site, which the row
+// then lists by index.  A row is written only when every circle of its star lies
+// inside the block (with a margin above the rounding of its centre and radius)
+// and its centre within L/8: no particle outside the block can then change it.
+// Everything else -- circles that reach out of the block, stars of more than 16
+// sites, rows longer than dmax, strips that could not be staged -- is listed for
 // k_vor_wave, which takes a wavefront per row, and what that leaves is flagged
 // for the general kernel.
 //
@@ -45,6 +46,7 @@ namespace nm {
 namespace {
 
 constexpr int kVsCap = 16;         // longest row
+constexpr int kVsTwin = 1 << 16;   // flag of a site with several particles
 constexpr double kVsReach = 2.6;   // block half side, in mean spacings
 
 // Dot product of two packed pairs of 16-bit values (below 2^31), with a zero
@@ -93,7 +95,8 @@ struct PivotStep {
 // together: 2^20 particles on a square lattice 254 us (375 with every candidate
 // of the block compared in integers, 249 by clipping alone), 2^18 on one a few
 // units out of place 264 (500, 362).
-// Returns the neighbour's LDS index, -1: none, -2: two particles at its position.
+// Returns the neighbour's LDS index (the first of its site), with kVsTwin where
+// others share its position; -1: none.
 template <bool kWide>
 __device__ __noinline__ int vor_pivot_exact(const int* lpos, int b, int e, int pq, int pqy, int pa, int ax, int ay,
                                             float lim) {
@@ -153,7 +156,7 @@ __device__ __noinline__ int vor_pivot_exact(const int* lpos, int b, int e, int p
   } else {
     for (int i = b; i < e; ++i) compare(i);
   }
-  return twin ? -2 : best;
+  return twin ? best | kVsTwin : best;
 }
 
 // The star of staged particle `self` over the candidates of its block, whose rows
@@ -161,10 +164,12 @@ __device__ __noinline__ int vor_pivot_exact(const int* lpos, int b, int e, int p
 // <= -gl or >= gr in x, <= -gd or >= gu in y.
 // Writes the neighbours' LDS indices to col[0 .. m) (stride kBlock),
 // counter-clockwise from the nearest; first: the entry to start the row at
-// (counter-clockwise from +x).  Returns m, or 0 when the row is not certain.
+// (counter-clockwise from +x); shared: particles share the own position or a
+// neighbour's.  Returns m, or 0 when the row is not certain.
 template <bool kWide>
 __device__ __forceinline__ int vor_star(const int* lpos, const int* rows, int lw, int self, int gl, int gr, int gd,
-                                        int gu, int cap, float domain, uint16_t* col, int& first) {
+                                        int gu, int cap, float domain, uint16_t* col, int& first,
+                                        bool& shared) {
   const int b = rows[0], e = rows[(gd + gu - 1) >> lw];
   const int2* lpos2 = reinterpret_cast<const int2*>(lpos);
   int pq, pqy = 0;
@@ -174,45 +179,41 @@ __device__ __forceinline__ int vor_star(const int* lpos, const int* rows, int lw
   } else {
     pq = lpos[self];
   }
-  // the nearest: fp32 squared distances will do on wide strips, since any
-  // particle whose disc on the segment is empty starts the star; the exact
-  // minimum is within rounding of the one found, so that choice is confirmed
-  // by taking exact distances there
-  int start = -1;
-  {
-    if (kWide) {
-      long long best = 1ll << 62;
-      for (int i = b; i < e; ++i) {
-        const int2 c = lpos2[i];
-        const long long dx = c.x - pq, dy = c.y - pqy;
-        const long long d2 = dx * dx + dy * dy;
-        if (i != self && d2 < best) {
-          best = d2;
-          start = i;
-        }
+  // the nearest other site, and how many particles are at the particle's own
+  int start = -1, own = 0;
+  if (kWide) {
+    unsigned long long best = ~0ull;
+    for (int i = b; i < e; ++i) {
+      const int2 c = lpos2[i];
+      const long long dx = c.x - pq, dy = c.y - pqy;
+      const unsigned long long d2 = static_cast<unsigned long long>(dx * dx + dy * dy);
+      own += d2 == 0ull ? 1 : 0;
+      if (d2 - 1ull < best) {  // (0: the largest)
+        best = d2 - 1ull;
+        start = i;
       }
-      if (best == 0) return 0;
-    } else {
-      uint32_t best = ~0u;
-      auto round = [&](int i, bool tail) {
-        int c[kUnroll];
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) c[u] = lpos[i + u];  // (buffer padded by kUnroll)
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-          uint32_t d2 = rel_d2_u(c[u], pq);
-          if (i + u == self || (tail && i + u >= e)) d2 = ~0u;
-          start = d2 < best ? i + u : start;
-          best = min(best, d2);
-        }
-      };
-      const int full = b + ((e - b) & ~(kUnroll - 1));
-      for (int i = b; i < full; i += kUnroll) round(i, false);
-      if (full < e) round(full, true);
-      if (best == 0u) return 0;
     }
-    if (start < 0) return 0;
+  } else {
+    uint32_t best = ~0u;
+    auto round = [&](int i, bool tail) {
+      int c[kUnroll];
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) c[u] = lpos[i + u];  // (buffer padded by kUnroll)
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) {
+        uint32_t d2 = rel_d2_u(c[u], pq) - 1u;  // (0: the largest)
+        if (tail && i + u >= e) d2 = ~0u - 1u;
+        own += d2 == ~0u ? 1 : 0;
+        start = d2 < best ? i + u : start;
+        best = min(best, d2);
+      }
+    };
+    const int full = b + ((e - b) & ~(kUnroll - 1));
+    for (int i = b; i < full; i += kUnroll) round(i, false);
+    if (full < e) round(full, true);
   }
+  if (start < 0 || start >= e) return 0;
+  shared = own > 1;
   int cur = start, m = 0;
   first = -1;
   for (;;) {
@@ -273,6 +274,10 @@ __device__ __forceinline__ int vor_star(const int* lpos, const int* rows, int lw
       const int hi = min(static_cast<int>(hy + r + static_cast<float>(gd)) >> lw, top);
       next = vor_pivot_exact<kWide>(lpos, rows[lo], rows[hi + 1], pq, pqy, pa, ax, ay, t0 + fabsf(t0) * 0x1p-19f);
       if (next < 0) return 0;
+      if (next & kVsTwin) {
+        shared = true;
+        next &= ~kVsTwin;
+      }
     }
     int bx, by;
     if (kWide) {
@@ -291,6 +296,58 @@ __device__ __forceinline__ int vor_star(const int* lpos, const int* rows, int lw
     cur = next;
   }
   return first < 0 ? 0 : m;
+}
+
+// The row of a star with shared sites: the other particles of the own site by
+// index, then each neighbour site's.  A site lies in one cell, so its particles
+// are among the staged ones of its halo row.  Returns the row's length, or 0,
+// with nothing written, where it exceeds dmax.  (2^20 particles in pairs: 2.3 ms,
+// as by clipping; 21 with a wavefront for each of their rows.)
+template <bool kWide>
+__device__ __noinline__ int vor_write_shared(const int* lpos, const int* lidx, const uint8_t* rowid, const int* rbase,
+                                             const uint16_t* col, int self, int m, int first, int dmax,
+                                             int32_t* __restrict__ row) {
+  using P = std::conditional_t<kWide, int2, int>;
+  const P* pos = reinterpret_cast<const P*>(lpos);
+  auto same = [&](int i, int j) {
+    if constexpr (kWide)
+      return pos[i].x == pos[j].x && pos[i].y == pos[j].y;
+    else
+      return pos[i] == pos[j];
+  };
+  const int who = lidx[self];
+  int len = 0;
+  for (int write = 0; write < 2; ++write) {
+    int at = 0;
+    for (int t = -1; t < m; ++t) {
+      int u = first + t;
+      u = u >= m ? u - m : u;
+      const int p = t < 0 ? self : col[u * kBlock];
+      const int b = rbase[rowid[p]], e = rbase[rowid[p] + 1];
+      if (write) {
+        for (int prev = -1;;) {
+          int next = 0x7FFFFFFF, left = 0;  // the next index, and how many remain
+          for (int i = b; i < e; ++i) {
+            const int j = lidx[i];
+            if (same(i, p) && j > prev && j != who) {
+              ++left;
+              next = min(next, j);
+            }
+          }
+          if (left == 0) break;
+          row[at++] = next;
+          if (left == 1) break;
+          prev = next;
+        }
+      } else {
+        for (int i = b; i < e; ++i) at += same(i, p) && i != self ? 1 : 0;
+      }
+    }
+    len = at;
+    if (len > dmax) return 0;
+  }
+  for (int u = len; u < dmax; ++u) row[u] = -1;
+  return len;
 }
 
 // Append slot s to the wave kernel's list (one atomic per wavefront).
@@ -440,9 +497,14 @@ __global__ __launch_bounds__(kBlock) void k_vor_strip(DevWs w, TileCfg tc, int d
             const int gl = rx + 1, gr = W * cw - rx;
             const int gd = oy + half * cw + 1, gu = (half + 1) * cw - oy;
             int first = 0;
+            bool shared = false;
             uint16_t* col = s_col + threadIdx.x;
-            const int m = vor_star<kWide>(lpos, s_rbase + cy - half, lw, self, gl, gr, gd, gu, cap, domain, col, first);
-            if (m > 0) {
+            int m = vor_star<kWide>(lpos, s_rbase + cy - half, lw, self, gl, gr, gd, gu, cap, domain, col, first, shared);
+            if (shared && m > 0) {
+              m = vor_write_shared<kWide>(lpos, lidx, s_rowid, s_rbase, col, self, m, first, dmax,
+                                          ring + static_cast<int64_t>(lidx[self]) * dmax);
+              if (m > 0) deg[lidx[self]] = m;
+            } else if (m > 0) {
               const int who = lidx[self];
               int32_t* row = ring + static_cast<int64_t>(who) * dmax;
               // four entries a store (rows start on any 4-byte boundary)
@@ -462,7 +524,8 @@ __global__ __launch_bounds__(kBlock) void k_vor_strip(DevWs w, TileCfg tc, int d
                 row[u] = u < m ? lidx[col[(p < m ? p : 0) * kBlock]] : -1;
               }
               deg[who] = m;
-            } else {
+            }
+            if (m == 0) {
               defer = true;
               s = strip_slot(StripLds{lpos_store, lidx, s_rbase, s_ga0, s_n0, s_ga1, s_qoff, s_tself, s_wsum,
                                       s_rowid, s_qmap},

@@ -640,3 +640,23 @@ def test_voronoi_strips_near_ties(rings, box, w, jitter):
     some = np.arange(0, len(x), 8, dtype=np.int32)
     got = _rows_of(ring, deg)
     assert [got[i] for i in some] == _oracle_rows(x, y, box, rows=some)
+
+
+# Coincident particles in rows from strips (16-bit and 32-bit offsets): sites of
+# one to four particles in shuffled order, rows that just fit dmax and that don't.
+@pytest.mark.parametrize("box,w", [(1 << 14, 1 << 9), (1 << 20, 1 << 15), (1 << 14, 1 << 7)])
+@pytest.mark.parametrize("most", [2, 4])
+def test_voronoi_strips_shared_sites(box, w, most):
+    rng = np.random.default_rng(most)
+    x, y, _ = workloads.uniform(700, box=box, seed_pos=most)
+    times = rng.integers(1, most + 1, 700) if most > 2 else np.full(700, 2)
+    x, y = np.repeat(x, times), np.repeat(y, times)
+    o = rng.permutation(len(x))
+    x, y = x[o], y[o]
+    ref = _oracle_rows(x, y, box)
+    longest = max(len(r) for r in ref)
+    for dmax in (longest, longest - 1):
+        ring, deg, st, _ = _gpu_rows(x, y, box, w, dmax=dmax)
+        assert st == (0 if dmax == longest else nm.NM_E_CAPACITY)
+        assert _rows_of(ring, deg) == [r[:dmax] for r in ref]
+        assert (ring[np.arange(dmax)[None, :] >= deg[:, None]] == -1).all()
