@@ -1086,8 +1086,15 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kKnnWave
 
 // Field-of-view lists over the same strips (a.theta: headings, a.cone: the
 // cone's cos(half angle) * 4096).
+// Two waves per SIMD asked of the compiler for the long lists, three for up to 12,
+// four for up to 4: left to itself it takes 256 registers, and one wave, for lists
+// of 20 (2^20 uniform particles, every direction: 290 us at two waves, 402 at one,
+// 358 at three, which spill; half plane 640 and 1070).
 template <int KMAX>
-__global__ __launch_bounds__(kBlock) void k_knn_fov_strip(DevWs w, FastCfg f, TileCfg tc, int k,
+constexpr int kFovWaves = KMAX <= 4 ? 4 : (KMAX <= 12 ? 3 : 2);
+
+template <int KMAX>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kFovWaves<KMAX>))) void k_knn_fov_strip(DevWs w, FastCfg f, TileCfg tc, int k,
                                                           int32_t* __restrict__ nbr, AlignArgs a) {
   knn_tile_body<KMAX, false, kFieldOfView, kStripPts>(w, f, tc, k, nbr, nullptr, a, xcd_run(blockIdx.x, gridDim.x));
 }
@@ -1168,7 +1175,8 @@ inline double solo_strip_queries(int n) {
 // `reach_x`: half width in mean k-th-neighbour radii; `pts`: particles staged.
 TileCfg tile_cfg_impl(const DevWs& w, const FastCfg& f, int k, bool narrow_strips, int pts, StripUse use = kUseBatch,
                       double reach_x = kReachX) {
-  const double queries = use == kUseSolo ? solo_strip_queries(w.n) : kStripQ;
+  const bool solo = use == kUseSolo || use == kUseSoloFov;
+  const double queries = solo ? solo_strip_queries(w.n) : kStripQ;
   TileCfg t{1, 1, 0, 0, w.G, w.G, 0, 0};
   const double rho = static_cast<double>(w.n) / static_cast<double>(w.C);  // particles per cell
   const double rr = rho > 1e-12 ? rho : 1e-12;
@@ -1213,8 +1221,12 @@ TileCfg tile_cfg_impl(const DevWs& w, const FastCfg& f, int k, bool narrow_strip
   // Sparse systems, whose blocks would span 2^15 units, take one column where
   // the rows allow: their buffer holds half the particles, and one column may
   // bring the block under the limit (k = 31, 200,000 particles: 626 -> 490 us
-  // clustered, 170 -> 163 uniform; k = 12, 50,000: 41 -> 33).
-  if (use == kUseSolo && (static_cast<long long>(tw + 2 * hx) << w.log2_w) >= 32768) {
+  // clustered, 170 -> 163 uniform; k = 12, 50,000: 41 -> 33).  Not the wide halos of
+  // field-of-view lists on systems that fill the device anyway, which one column
+  // stages for few queries (300,000 uniform particles, k = 20, 43 degrees: 1.28 ms
+  // with one column, 1.01 with two; 20,000, k = 16: 139 us and 161).
+  const bool one = use == kUseSolo || (use == kUseSoloFov && (hx <= 4 || w.n < 65536));
+  if (one && (static_cast<long long>(tw + 2 * hx) << w.log2_w) >= 32768) {
     tw = 1;
     widen();
   }
@@ -1360,7 +1372,7 @@ hipError_t launch_knn_fov_strips(const DevWs& w, int block, const float* theta, 
   const double alpha = acos(fmax(-1.0, fmin(1.0, c / 4096.0)));
   const double frac = fmax(alpha / 3.141592653589793, 1.0 / 64.0);
   const int ks = static_cast<int>(ceil(k / frac));
-  const TileCfg tc = tile_cfg_impl(w, f, ks, true, kStripPts, kUseSolo);
+  const TileCfg tc = tile_cfg_impl(w, f, ks, true, kStripPts, kUseSoloFov);
   f.reach = static_cast<float>(f.reach * sqrt(static_cast<double>(ks) / k));
   AlignArgs a{};
   a.theta = theta;

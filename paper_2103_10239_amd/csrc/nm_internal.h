@@ -657,7 +657,7 @@ hipError_t launch_metric_fill(const DevWs& w, long long rc2, const int32_t* offs
 hipError_t launch_scan_rows(int32_t* data, int64_t m, ScanState* st, int nb, WsHeader* hdr,
                             hipStream_t s);
 // Who runs a system's strips (they are sized for it).
-enum StripUse { kUseBatch = 0, kUseSolo, kUseServed };
+enum StripUse { kUseBatch = 0, kUseSolo, kUseSoloFov, kUseServed };
 TileCfg tile_cfg(const DevWs& w, const FastCfg& f, int k, StripUse use = kUseBatch);
 // Host-only description of the k-NN kernel a grid runs (nm_knn_layout).
 void knn_layout(const DevWs& w, int k, int block, int32_t out[10]);
