@@ -67,26 +67,67 @@ __device__ __forceinline__ bool knn_exact(const DevWs& w, int s, int qx, int qy,
   return top.worst() != ~0ull;
 }
 
+// Ascending order of eight keys and what they carry (Batcher's network of 19).
+__device__ __forceinline__ bool sort_eight(unsigned long long (&key)[8], int (&v)[8]) {
+  constexpr int net[19][2] = {{0, 1}, {2, 3}, {4, 5}, {6, 7}, {0, 2}, {1, 3}, {4, 6}, {5, 7}, {1, 2}, {5, 6},
+                              {0, 4}, {1, 5}, {2, 6}, {3, 7}, {2, 4}, {3, 5}, {1, 2}, {3, 4}, {5, 6}};
+  bool moved = false;
+#pragma unroll
+  for (int c = 0; c < 19; ++c) {
+    const int i = net[c][0], j = net[c][1];
+    const bool swap = key[j] < key[i];
+    const unsigned long long ki = key[i], kj = key[j];
+    const int vi = v[i], vj = v[j];
+    key[i] = swap ? kj : ki;
+    key[j] = swap ? ki : kj;
+    v[i] = swap ? vj : vi;
+    v[j] = swap ? vi : vj;
+    moved = moved || swap;
+  }
+  return moved;
+}
+
 // Reorder neighbours whose distance fields tie (or lie too close for their
 // order to be certain) by the exact (d^2, index): bit t of `link` says that
-// entries t and t + 1 do, the linked runs are sorted by passes of exchanges
-// between linked entries.  exact(v) gives an entry's 64-bit key.  Runs of two
-// are the rule, so no key outside a run is ever formed (sorting all k by 64-bit
-// keys held 64 registers at k = 32).
+// entries t and t + 1 do.  exact(v) gives an entry's 64-bit key; entries before
+// `first` are unused.  Windows of eight entries, four apart, that hold a link
+// are sorted by their exact keys, which agree with the fields' order everywhere
+// else; runs of up to five lie within one window, longer ones take passes until
+// nothing moves.  (All entries sorted at once held 64 registers at k = 32; each
+// linked pair compared in turn, passes until nothing moved, is a chain of LDS
+// reads: lists on a square lattice of 1024, k = 24 48 us, 25 so; k = 8 16 and 11;
+// of 2^16, k = 24 74 and 49.)
 template <int KMAX, class Exact>
-__device__ __forceinline__ void sort_linked(uint32_t link, int (&v)[KMAX], Exact&& exact) {
+__device__ __forceinline__ void sort_linked(uint32_t link, int first, int (&v)[KMAX], Exact&& exact) {
+  const bool longer = (link & (link >> 1) & (link >> 2) & (link >> 3) & (link >> 4)) != 0u;
+  auto key_of = [&](int t) { return t >= KMAX ? ~0ull : (t < first ? 0ull : exact(v[t < KMAX ? t : 0])); };
   bool again = true;
   while (again) {
     again = false;
+    unsigned long long key[8] = {};
+    bool carried = false;  // key[4 .. 7] are those of this window's first four
 #pragma unroll
-    for (int t = 0; t + 1 < KMAX; ++t) {
-      if ((link >> t) & 1u) {
-        if (exact(v[t + 1]) < exact(v[t])) {
-          const int s = v[t];
-          v[t] = v[t + 1];
-          v[t + 1] = s;
-          again = true;
+    for (int t0 = 0; t0 == 0 || t0 + 4 < KMAX; t0 += 4) {
+      if ((link >> t0) & 0x7Fu) {
+        int w[8];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) key[u] = key[u + 4];
+        if (!carried) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) key[u] = key_of(t0 + u);
         }
+#pragma unroll
+        for (int u = 4; u < 8; ++u) key[u] = key_of(t0 + u);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) w[u] = v[t0 + u < KMAX ? t0 + u : KMAX - 1];
+        const bool moved = sort_eight(key, w);
+        again = again || (longer && moved);
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (t0 + u < KMAX) v[t0 + u < KMAX ? t0 + u : 0] = w[u];
+        carried = true;
+      } else {
+        carried = false;
       }
     }
   }
@@ -238,7 +279,7 @@ __device__ __forceinline__ bool knn_fast(const DevWs& w, const FastCfg& f, int s
     }
     if (mapped && link != 0u) {
       const int shx = 32 - w.log2_box;
-      sort_linked<KMAX>(link, slot, [&](int q) {
+      sort_linked<KMAX>(link, KMAX - k, slot, [&](int q) {
         const int4 e = w.sorted[q];
         const long long ex = wrap_axis(e.x - qx, shx), ey = wrap_axis(e.y - qy, shx);
         return pack_key(ex * ex + ey * ey, e.z);
@@ -524,7 +565,7 @@ __device__ __forceinline__ bool strip_search(const DevWs& w, const TileCfg& tc, 
     for (int t = 0; t < KMAX; ++t)
       if (t >= KMAX - k) lds[t] = static_cast<int>(key[t] & 0x1FFFu);
     if (link != 0u)
-      sort_linked<KMAX>(link, lds, [&](int i) { return pack_key(staged_d2<kWide>(lpos, i, pq, pqy), lidx[i]); });
+      sort_linked<KMAX>(link, KMAX - k, lds, [&](int i) { return pack_key(staged_d2<kWide>(lpos, i, pq, pqy), lidx[i]); });
     return true;
   }
   return false;

@@ -1002,3 +1002,27 @@ def test_metric_list_without_cells_is_refused_whatever_the_lists_hold():
         assert nm.check(ws) == nm.NM_E_INVAL
         assert (offs == 0).all() and (idx == -7).all()
         h[list(words)] = 0
+
+
+# Runs of ties of every length within lists: groups of k + 1 particles on a few
+# sites, far apart, so that a list is its group and only the index orders most of
+# it; in strips of 16-bit and of 32-bit offsets and from global memory.
+@pytest.mark.parametrize("k,sites", [(1, (2,)), (2, (1, 2)), (4, (2, 3)), (6, (7,)), (7, (3, 5)), (7, (8,)), (8, (4, 5)),
+                                     (11, (5, 7)), (12, (6, 7)), (16, (17,)), (19, (6, 6, 8)), (20, (9, 12)),
+                                     (24, (8, 8, 9)), (31, (6, 9, 17)), (31, (32,)), (32, (4, 13, 16))])
+@pytest.mark.parametrize("w,block", [(1 << 10, 0), (1 << 10, nm.NM_BLOCK_SUBSTRIPS), (1 << 10, 3), (1 << 15, 0),
+                                     (1 << 15, nm.NM_BLOCK_SUBSTRIPS)])
+def test_knn_runs_of_ties(k, sites, w, block):
+    box = 32 * w
+    gx, gy = np.meshgrid(np.arange(0, 32, 4), np.arange(0, 32, 4))
+    at = np.repeat(np.cumsum(np.arange(len(sites))), sites)  # sites at 0, 1, 3, ...
+    x = (gx.reshape(-1, 1) * w + w // 2 + 8 * at[None, :]).reshape(-1)
+    y = (gy.reshape(-1, 1) * w + w // 3 + 5 * at[None, :]).reshape(-1)
+    o = np.random.default_rng(k).permutation(len(x))
+    x, y = x[o].astype(np.int32), y[o].astype(np.int32)
+    ws = nm.Workspace(len(x), box, w, block=block)
+    nm.build_cells(ws, _dev(x, torch.int32), _dev(y, torch.int32))
+    nbr, d2 = nm.knn(ws, k, with_d2=True)
+    assert nm.check(ws) == 0
+    rn, rd = oracle.knn(x, y, box, k)
+    assert np.array_equal(nbr.cpu().numpy(), rn) and np.array_equal(d2.cpu().numpy(), rd)
