@@ -781,6 +781,12 @@ __device__ __forceinline__ bool inc_positive(double na, double nb, double nc, do
   return big(na) * big(bc) + big(nb) * big(ca) + big(nc) * big(ab) > 0;
 }
 
+// Row a (m entries) holds the site of b followed directly by that of i.
+__device__ __noinline__ bool vor_row_follows(const int32_t* __restrict__ x, const int32_t* __restrict__ y, int dmax,
+                                             const int32_t* __restrict__ row, int m, int a, int b, int i) {
+  return row_holds_then(row_view(row, m, a, x, y, dmax), x[b], y[b], x[i], y[i]);
+}
+
 // Rows of up to this many entries without coincident particles take the
 // straight path (longer ones are one row in ten thousand of a uniform system).
 constexpr int kRowFast = 12;
@@ -789,8 +795,7 @@ constexpr int kRowFast = 12;
 // registers under fixed indices (a walk by index costs a select over the row
 // per access), the norms and cross products shared between neighbouring
 // triangles, incircle signs from fp64.  Returns false where the general test
-// has to decide (long rows, coincident particles, a row that does not list
-// the triangle entry by entry).
+// has to decide (long rows, coincident particles).
 __device__ __forceinline__ bool vor_check_fast(const int32_t* __restrict__ x, const int32_t* __restrict__ y, int n,
                                                int log2_box, int dmax, const int32_t* __restrict__ ring,
                                                const int32_t* __restrict__ deg, int i, RowCheck& out) {
@@ -827,7 +832,16 @@ __device__ __forceinline__ bool vor_check_fast(const int32_t* __restrict__ x, co
     ox[u] = wrap_axis(ox[u] - xi, sh);
     oy[u] = wrap_axis(oy[u] - yi, sh);
   }
-  bool fail = false, twin = false;
+  // (coincident particles: the general test, before any arithmetic here)
+  bool twin = false;
+#pragma unroll
+  for (int u = 0; u < kRowFast; ++u) {
+    const int v = u + 1 < kRowFast ? u + 1 : 0;
+    const int nx = u + 1 < m ? ox[v] : ox[0], ny = u + 1 < m ? oy[v] : oy[0];
+    if (u < m) twin = twin || (ox[u] == 0 && oy[u] == 0) || (ox[u] == nx && oy[u] == ny);
+  }
+  if (twin) return false;
+  bool fail = false;
   int wraps = 0, turn = 0;
   double area2 = 0.0;  // integers below 2^45
   double ax = ox[0], ay = oy[0], bx = ox[1], by = oy[1];
@@ -842,7 +856,6 @@ __device__ __forceinline__ bool vor_check_fast(const int32_t* __restrict__ x, co
       const double cx = cxi, cy = cyi;
       const double nc = cx * cx + cy * cy, bc = bx * cy - by * cx, ca = cx * ay - cy * ax;
       if (abs(ox[u]) >= quarter || abs(oy[u]) >= quarter) fail = true;
-      twin = twin || na == 0.0 || (ax == bx && ay == by);
       if (!(ab > 0.0)) fail = true;
       area2 += ab;
       if (!ccw_before(static_cast<int>(ax), static_cast<int>(ay), static_cast<int>(bx), static_cast<int>(by))) {
@@ -859,7 +872,6 @@ __device__ __forceinline__ bool vor_check_fast(const int32_t* __restrict__ x, co
       ab = bc;
     }
   }
-  if (twin) return false;
   if (wraps != 1) fail = true;
   // entry u's row must list entry u + 1 directly followed by i; the rows (and
   // lengths) of kRowBatch entries are read together
@@ -911,8 +923,9 @@ __device__ __forceinline__ bool vor_check_fast(const int32_t* __restrict__ x, co
             next = next || (at(v) == b && nx == i);
           }
         }
-        if (!in) fail = true;
-        if (!next) unlisted = true;
+        // (a row that lists other particles of these sites, or not the triangle)
+        if (!in || (!next && !vor_row_follows(x, y, dmax, ring + static_cast<long long>(a) * dmax, mc, a, b, i)))
+          fail = true;
       }
     }
   }
@@ -1092,7 +1105,7 @@ __global__ __launch_bounds__(kBlock) void k_vor_total(DevWs w, int nb, int32_t* 
   s_area[threadIdx.x] = area;
   s_fail[threadIdx.x] = fails;
   __syncthreads();
-  for (int h = kBlock / 2; h > 0; h >>= 1) {
+  for (int h = nb > 0 ? kBlock / 2 : 0; h > 0; h >>= 1) {
     if (static_cast<int>(threadIdx.x) < h) {
       s_area[threadIdx.x] += s_area[threadIdx.x + h];
       s_fail[threadIdx.x] += s_fail[threadIdx.x + h];
@@ -1145,7 +1158,7 @@ hipError_t launch_voronoi_check(const DevWs& w, const int32_t* x, const int32_t*
   const int nb = (w.n + kBlock - 1) / kBlock;
   hipLaunchKernelGGL(k_vor_clear, dim3(nb), dim3(kBlock), 0, s, w.hdr, stale, w.n, 0);
   hipLaunchKernelGGL(k_vor_check<false>, dim3(nb), dim3(kBlock), 0, s, x, y, w, dmax, ring, deg, stale, nullptr, 0);
-  hipLaunchKernelGGL(k_vor_total, dim3(1), dim3(kBlock), 0, s, w, 0, nfail, 0, 0);
+  hipLaunchKernelGGL(k_vor_total, dim3(1), dim3(64), 0, s, w, 0, nfail, 0, 0);
   return hipGetLastError();
 }
 
