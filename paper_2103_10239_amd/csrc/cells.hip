@@ -56,6 +56,7 @@ __device__ __forceinline__ void ws_init_body(const DevWs& w, int b, int nb) {
       w.hdr->nvgo = 0u;
       w.hdr->nvfull = 0u;
       w.hdr->nvkeep = 0u;
+      w.hdr->nvflag = 0u;
       w.hdr->varea2 = 0ull;
       w.hdr->off_start = reinterpret_cast<char*>(w.start) - reinterpret_cast<char*>(w.hdr);
       w.hdr->off_sorted = reinterpret_cast<char*>(w.sorted) - reinterpret_cast<char*>(w.hdr);

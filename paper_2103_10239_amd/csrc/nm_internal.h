@@ -61,7 +61,7 @@ struct WsHeader {
   uint32_t nvgo;       // rows failed in the update's last reuse test
   uint32_t nvfull;     // the update rebuilds every row
   uint32_t nvkeep;     // ... and kept some that it could not
-  uint32_t pad0;
+  uint32_t nvflag;     // some row is flagged (dflag) for the general kernel
   int64_t off_start;   // bytes from here to start and sorted, for calls that get
   int64_t off_sorted;  // the workspace without its grid
   unsigned long long varea2;  // sum over Voronoi rows of a_t x a_{t+1} (the reuse test alone)

@@ -475,6 +475,7 @@ __global__ __launch_bounds__(kVnBlock) void k_voronoi(DevWs w, int dmax, int32_t
 // an update that rebuilt every row is done unless rows were kept.
 __device__ __forceinline__ void general_done(WsHeader* h) {
   h->nvstale = 0u;  // (the narrow kernel's list)
+  h->nvflag = 0u;
   if (h->nvfull != 0u) {
     const uint32_t kept = h->nvkeep;
     h->nvfail = kept;
@@ -1134,7 +1135,7 @@ hipError_t launch_general(const DevWs& w, int dmax, int32_t* ring, int32_t* deg,
   const int nb = (w.n + kVnBlock - 1) / kVnBlock;
   if (flagged)
     hipLaunchKernelGGL(k_voronoi, dim3(nb), dim3(kVnBlock), 0, s, w, dmax, ring, deg, nullptr, nullptr, 1,
-                       &w.hdr->nvstale, stale);
+                       &w.hdr->nvflag, stale);
   else
     hipLaunchKernelGGL(k_voronoi, dim3(nb), dim3(kVnBlock), 0, s, w, dmax, ring, deg, every ? nullptr : w.rank,
                        every ? nullptr : &w.hdr->nvstale, 0, gate, nullptr);

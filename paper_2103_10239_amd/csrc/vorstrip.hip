@@ -46,6 +46,12 @@ namespace nm {
 namespace {
 
 constexpr int kVsCap = 16;         // longest row
+// Candidates of a block above which a row goes to the general kernel at once: a
+// star costs its candidates times its steps, clipping each candidate about once,
+// but has a cell's latency.  Rows of 2^20 particles, half of them in 64 clusters,
+// with 900, without a limit, by clipping alone: eight particles a cell 10.5, 14.1
+// and 11.1 ms, two a cell 2.5, 2.5 and 5.1 (4.2 with a limit of 400 or 600).
+constexpr int kVsCands = 900;
 constexpr int kVsTwin = 1 << 16;   // flag of a site with several particles
 constexpr double kVsReach = 2.6;   // block half side, in mean spacings
 
@@ -499,7 +505,10 @@ __global__ __launch_bounds__(kBlock) void k_vor_strip(DevWs w, TileCfg tc, int d
             int first = 0;
             bool shared = false;
             uint16_t* col = s_col + threadIdx.x;
-            int m = vor_star<kWide>(lpos, s_rbase + cy - half, lw, self, gl, gr, gd, gu, cap, domain, col, first, shared);
+            const int* rows = s_rbase + cy - half;
+            const bool dense = rows[2 * half + 1] - rows[0] > kVsCands;
+            int m = 0;
+            if (!dense) m = vor_star<kWide>(lpos, rows, lw, self, gl, gr, gd, gu, cap, domain, col, first, shared);
             if (shared && m > 0) {
               m = vor_write_shared<kWide>(lpos, lidx, s_rowid, s_rbase, col, self, m, first, dmax,
                                           ring + static_cast<int64_t>(lidx[self]) * dmax);
@@ -526,10 +535,14 @@ __global__ __launch_bounds__(kBlock) void k_vor_strip(DevWs w, TileCfg tc, int d
               deg[who] = m;
             }
             if (m == 0) {
-              defer = true;
+              defer = !dense;
               s = strip_slot(StripLds{lpos_store, lidx, s_rbase, s_ga0, s_n0, s_ga1, s_qoff, s_tself, s_wsum,
                                       s_rowid, s_qmap},
                              self);
+              if (dense) {
+                w.dflag[s] = 1;
+                w.hdr->nvflag = 1u;
+              }
             }
           } else {
             int r = 0;
@@ -820,7 +833,10 @@ __global__ __launch_bounds__(64 * kVwWaves) void k_vor_wave(DevWs w, int dmax, i
       if (lane == 0) deg[q.z] = row_len;
       done = true;
     }
-    if (!done && lane == 0) w.dflag[s] = 1;  // for the general kernel
+    if (!done && lane == 0) {  // for the general kernel
+      w.dflag[s] = 1;
+      w.hdr->nvflag = 1u;
+    }
     __builtin_amdgcn_wave_barrier();
   }
 }
