@@ -257,7 +257,8 @@ int nm_voronoi(const nm_grid* g, void* ws, int32_t dmax, int32_t* ring, int32_t*
  *          and every particle of its row (the rows a flip may change)
  *   nfail  device int32 or NULL, out: how many particles failed; 0 means
  *          no recomputation is needed
- * ws (grid g, n particles) holds the counters only. */
+ * ws holds the counters only: its cells are not read, and nothing beyond its
+ * header is written. */
 int nm_voronoi_check(const nm_grid* g, void* ws, const int32_t* x, const int32_t* y, int32_t dmax,
                      const int32_t* ring, const int32_t* deg, uint8_t* stale, int32_t* nfail,
                      void* stream);
@@ -297,7 +298,11 @@ typedef struct nm_vm_params {
  *   ws_err               workspace whose error word receives NM_E_INVAL for
  *                        rows that are not one triangulation and NM_E_RANGE
  *                        for coincident particles (the model needs a cell per
- *                        particle), or NULL
+ *                        particle), or NULL.  Where it holds cells of n
+ *                        particles (of these positions, for speed; the results
+ *                        do not depend on them) the particles are taken in
+ *                        their order, so the call has to be ordered with what
+ *                        builds cells there, as all calls on a workspace
  * box is L (power of two, 8 <= L <= 2^20). */
 int nm_voronoi_forces(const int32_t* x, const int32_t* y, int32_t n, int32_t box, int32_t dmax,
                       const int32_t* ring, const int32_t* deg, const nm_vm_params* vp, double* area,

@@ -249,7 +249,9 @@ def voronoi_update(ws: Workspace, x, y, ring, deg, stale: torch.Tensor | None = 
 def voronoi_forces(x, y, box: int, ring, deg, ka: float, kp: float, a0: float, p0: float,
                    energy: bool = True, vertices: bool = False, ws: Workspace | None = None) -> dict:
     """Voronoi model (Sec. V) on the rows of voronoi(): device tensors area, perim,
-    fx, fy [n] (fp64), energy [1] and, with vertices, [n, dmax, 4] (hx, hy, fx, fy)."""
+    fx, fy [n] (fp64), energy [1] and, with vertices, [n, dmax, 4] (hx, hy, fx, fy).
+    ws: receives errors; where it holds cells of n particles, those are taken in
+    their order (the results are the same without, the memory accesses are not)."""
     n = int(x.numel())
     dmax = int(ring.shape[1])
     dev = x.device

@@ -660,3 +660,30 @@ def test_voronoi_strips_shared_sites(box, w, most):
         assert st == (0 if dmax == longest else nm.NM_E_CAPACITY)
         assert _rows_of(ring, deg) == [r[:dmax] for r in ref]
         assert (ring[np.arange(dmax)[None, :] >= deg[:, None]] == -1).all()
+
+
+# Both ways an update goes on strips, each shown to be taken by the first test's
+# count: rounds of stale rows while at most one row in 512 fails, every row at
+# once beyond; the rows are those of a build from nothing.
+@pytest.mark.parametrize("moved,rounds", [(1, True), (4, True), (8, True), (400, False), (1 << 16, False)])
+@pytest.mark.parametrize("box,w", [(1 << 18, 1 << 10), (1 << 20, 1 << 13)])
+def test_update_takes_rounds_or_all_rows(moved, rounds, box, w):
+    n = 1 << 16
+    x, y, _ = workloads.uniform(n, box=box, seed_pos=94)
+    X, Y = _dev(x, torch.int32), _dev(y, torch.int32)
+    ws = nm.Workspace(n, box, w)
+    nm.build_cells(ws, X, Y)
+    R, D = nm.voronoi(ws, 24)
+    assert nm.check(ws) == 0
+    rng = np.random.default_rng(moved)
+    x1, y1 = x.copy(), y.copy()
+    who = rng.choice(n, moved, replace=False)
+    x1[who] = (x1[who] + rng.integers(1, box // 256, moved)) % box
+    X1, Y1 = _dev(x1, torch.int32), _dev(y1, torch.int32)
+    nm.build_cells(ws, X1, Y1)
+    nfail = int(nm.voronoi_update(ws, X1, Y1, R, D).item())
+    assert nm.check(ws) == 0
+    assert 0 < nfail * 512 <= n if rounds else nfail * 512 > n
+    R1, D1 = nm.voronoi(ws, 24)
+    assert nm.check(ws) == 0
+    assert torch.equal(R, R1) and torch.equal(D, D1)
