@@ -1204,6 +1204,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kBatchKn
 // k = 12: 41 and 32; 130,000: 49 with 256, 41 with 128, 58 with 64; larger
 // systems fill the device and stage less with 256, and up to some 4000
 // particles the few strips take one strip's latency whatever their size).
+// Uniform systems alone would do with larger strips from half of these limits on
+// (lists of 85,000, k = 12: 30 us with 64, 24 with 128 or 256; of 210,000, k = 1:
+// 16.5 with 128, 14.4 with 256), but smaller strips overflow the staging buffer
+// less often where particles cluster: 99,999, k = 20, 82 us with 64, 167 with 128;
+// 262,143, k = 7, 72 with 128, 189 with 256.
 inline double solo_strip_queries(int n) {
   return n < 4096 ? kStripQ : (n < 100000 ? 64.0 : (n < 262144 ? 128.0 : kStripQ));
 }

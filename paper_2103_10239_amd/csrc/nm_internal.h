@@ -149,10 +149,10 @@ __device__ __forceinline__ int xcd_tile(int b, int nb) {
 
 // As xcd_tile, in runs of kXcdRun tiles that go to the XCDs in turn: with one
 // stretch each the XCD with the densest stretch, or the slowest, finishes last,
-// and single tiles share no L2.  One stretch, runs of 64, 16, 8, 4 and 1: steps
-// of 2^20 uniform particles 92, 89, 89, 90, 94 and 114 us, of 2^22 clustered
-// 2060, 2216, 2069, 2035, 2023 and 2062, field-of-view lists of 300,007
-// 104, 97, 90, 88, 88 and 92.
+// and single tiles share no L2.  One stretch, runs of 64, 16, 8, 4 and 1, the
+// strip kernel's time: steps of 2^20 uniform particles 92, 89, 89, 90, 94 and
+// 114 us, of 2^22 clustered 2060, 2216, 2069, 2035, 2023 and 2062, field-of-view
+// lists of 300,007 104, 97, 90, 88, 88 and 92.
 constexpr int kXcdRun = 8;
 
 __device__ __forceinline__ int xcd_run(int b, int nb) {

@@ -29,11 +29,11 @@
 // by index through rows in registers or memory: forces 200 us at 250,000
 // particles and 1.30 ms at 2^20, cells 30 and 140 us.  With eight lanes the
 // vertices' gathers are in flight together: 90 and 350 us, 27 and 107 us.  At
-// 2^20 the force pass moves 1.5 GB from the memory-side cache into the L2s (12
-// lines a particle, each in a line of 128 bytes of its own) and issues VALU
-// instructions for half its time.  Errors against 80-bit arithmetic, 60,000
-// particles, relative to the root mean square force: mean 1.9e-16 and 99.9%
-// below 4.3e-15, as with a lane per particle (1.9e-16, 4.7e-15).
+// 2^20 the force pass moves 1.4 GB from the memory-side cache into the L2s (10
+// lines of 128 bytes a particle) and issues VALU instructions for 40% of its
+// time.  Errors against 80-bit arithmetic, 60,000 particles, relative to the root
+// mean square force: mean 1.9e-16 and 99.9% below 4.3e-15, as with a lane per
+// particle (1.9e-16, 4.7e-15).
 #include "nm_internal.h"
 
 namespace nm {

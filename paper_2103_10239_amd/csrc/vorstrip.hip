@@ -32,13 +32,12 @@
 //
 // Bound by VALU issue: about 17 instructions per candidate and step, 56
 // candidates and 6 steps per particle at the mean (the longest row of a
-// wavefront, 9 to 10, sets its steps): 12,550 instructions a wave, issued 84%
-// of the time, 54% of the lanes active.  Offsets of more than 16 bits (sparse
-// systems) take fp32 sums of products with their rounding put back (60,000
-// particles, 256 queries a strip: 106 us, 115 with fp64 products and their
-// conversions).  Rows of 2^20 uniform particles: 1.95
-// ms by clipping alone, 0.53 ms so (0.49 the strips, 0.02 the rows they
-// leave); of 250,000: 633 us, now 172 + 29.
+// wavefront, 9 to 10, sets its steps): 12,700 instructions a wave, 51% of the
+// lanes active.  Offsets of more than 16 bits (sparse systems) take fp32 sums of
+// products with their rounding put back (60,000 particles, 256 queries a strip:
+// 106 us, 115 with fp64 products and their conversions).  Rows of 2^20 uniform
+// particles, four a cell: 1.83 ms by clipping alone, 0.74 the strips and 0.03 the
+// rows they leave, one a cell 0.44; of 250,000: 633 us, now 150 + 27.
 #include "strip.h"
 
 namespace nm {
@@ -49,8 +48,8 @@ constexpr int kVsCap = 16;         // longest row
 // Candidates of a block above which a row goes to the general kernel at once: a
 // star costs its candidates times its steps, clipping each candidate about once,
 // but has a cell's latency.  Rows of 2^20 particles, half of them in 64 clusters,
-// with 900, without a limit, by clipping alone: eight particles a cell 10.5, 14.1
-// and 11.1 ms, two a cell 2.5, 2.5 and 5.1 (4.2 with a limit of 400 or 600).
+// with 900, without a limit, by clipping alone: 16 particles a cell 10.5, 14.1
+// and 11.1 ms, four a cell 2.5, 2.5 and 5.1 (4.2 with a limit of 400 or 600).
 constexpr int kVsCands = 900;
 constexpr int kVsTwin = 1 << 16;   // flag of a site with several particles
 constexpr double kVsReach = 2.6;   // block half side, in mean spacings
