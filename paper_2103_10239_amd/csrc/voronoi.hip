@@ -499,6 +499,8 @@ __global__ __launch_bounds__(kVwBlock) void k_voronoi_wide(DevWs w, int dmax, in
     return;
   }
   const int per = min(kVwRows, (nl + static_cast<int>(gridDim.x) - 1) / static_cast<int>(gridDim.x));
+  const uint32_t busy = static_cast<uint32_t>(min(static_cast<int>(gridDim.x), (nl + per - 1) / per));
+  if (blockIdx.x >= busy) return;  // (and is not counted below: one address for all)
   for (int k0 = blockIdx.x * per; k0 < nl; k0 += gridDim.x * per) {
     const int k = k0 + threadIdx.x;
     if (static_cast<int>(threadIdx.x) >= per || k >= nl) continue;
@@ -510,7 +512,7 @@ __global__ __launch_bounds__(kVwBlock) void k_voronoi_wide(DevWs w, int dmax, in
   __syncthreads();
   if (threadIdx.x == 0) {
     __threadfence();
-    if (atomicAdd(&w.hdr->nvdone, 1u) == gridDim.x - 1) {
+    if (atomicAdd(&w.hdr->nvdone, 1u) == busy - 1u) {
       w.hdr->nvwide = 0u;
       w.hdr->nvdone = 0u;
       __threadfence();
